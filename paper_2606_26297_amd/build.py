@@ -21,7 +21,7 @@ ARCH = "gfx950"
 
 HIP_SOURCES = ["qq_kernels.hip", "qq_fast.hip", "qq_many.hip", "qq_optim.hip", "qq_plain.hip", "qq_sample.hip",
                "qq_telegate.hip", "qq_static.hip"]
-CPP_SOURCES = ["qq_api.cpp", "qq_driver.cpp", "qq_alloc.cpp"]
+CPP_SOURCES = ["qq_api.cpp", "qq_driver.cpp", "qq_alloc.cpp", "qq_pool.cpp"]
 
 COMMON = ["-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function"]
 # Device code: gfx950 only; packed FP32 instructions disabled.

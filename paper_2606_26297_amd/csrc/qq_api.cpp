@@ -20,6 +20,7 @@
 #include <vector>
 
 #include "qq_internal.h"
+#include "qq_pool.h"
 
 using namespace qq;
 
@@ -122,14 +123,6 @@ hipError_t prof_aux(int kind, int n, int diag_bytes, double bytes, hipStream_t s
     return hipSuccess;
 }
 
-struct DevBuf {
-    void *p = nullptr;
-    ~DevBuf()
-    {
-        if (p) (void)hipFree(p);
-    }
-};
-
 }  // namespace
 
 struct qq_problem {
@@ -148,7 +141,10 @@ struct qq_problem {
     std::vector<int32_t> pair_ij;
     std::vector<double> pair_b;
     std::vector<int32_t> pair_bi;
-    // device copies
+    // device copies: the diagonal, the coefficient lists with the tables' per-thread constants (one
+    // block), the cost tables
+    DevBuf diag_buf, coef_buf, ctab_buf;
+    bool counted = false;  // in the pool's count of live problems
     void *d_diag = nullptr;
     double *d_ell = nullptr;
     int32_t *d_ell_i = nullptr;
@@ -184,25 +180,28 @@ struct qq_problem {
     int graphs = 0;
     // Per-tile cost tables of the complex64 per-pass kernels (launch_cost_table), in one allocation: one
     // per tile geometry (high, pos4, pos8) of every set plan and per cost layout (the tile's lane and wave
-    // qubits at lane_q, its register qubits at the other run); each is [tiles][kCostRow] rows followed
-    // by the per-thread constants [256][8].  Built once at creation, so no evaluation allocates for them.
+    // qubits at lane_q, its register qubits at the other run): [tiles][kCostRow] rows, with per-thread
+    // constants [256][8] kept apart.  Built once at creation, so no evaluation allocates for them.
     struct CostTab {
         int high, pos4, pos8, lane_q;
-        size_t off;  // in doubles from d_ctab
+        const double *rows, *thr;  // device
     };
     std::vector<CostTab> ctabs;
-    double *d_ctab = nullptr;
     // the same tables of the cross-QPU couplings alone (qq_set_allocation), read by the partitioned phases
     std::vector<CostTab> xtabs;
-    double *d_xtab = nullptr;
+    DevBuf xtab_buf, xthr_buf;
 
     ~qq_problem()
     {
-        void *ptrs[] = {d_diag, d_ell, d_ell_i, d_pair_ij, d_pair_b, d_pair_bi, d_regq, d_part_cq, d_qpu, d_tables, d_cross,
-                        d_part, d_ctab, d_xtab};
+        void *ptrs[] = {d_part_cq, d_qpu, d_tables, d_cross, d_part};
         if (dim) (void)hipSetDevice(device);
         for (void *q : ptrs)
             if (q) (void)hipFree(q);
+        // evaluations on the caller's streams may still read the handle's memory
+        if (diag_buf.p && hipDeviceSynchronize() == hipSuccess)
+            for (DevBuf *b : {&diag_buf, &coef_buf, &ctab_buf, &xtab_buf, &xthr_buf}) b->done();
+        for (DevBuf *b : {&diag_buf, &coef_buf, &ctab_buf, &xtab_buf, &xthr_buf}) b->release();
+        if (counted) pool_problem_removed(device);
     }
 };
 
@@ -610,7 +609,7 @@ std::vector<qq_problem::CostTab> cost_table_list(int n)
     auto add = [&](const SetDesc &sd, int lane_q) {
         for (const auto &t : tabs)
             if (t.high == sd.high && t.pos4 == sd.pos4 && t.pos8 == sd.pos8 && t.lane_q == lane_q) return;
-        tabs.push_back({sd.high, sd.pos4, sd.pos8, lane_q, 0});
+        tabs.push_back({sd.high, sd.pos4, sd.pos8, lane_q, nullptr, nullptr});
     };
     for (int pr = 0; pr < (pairing_applies(n) ? kPairings : 1); ++pr)
         for (const SetDesc &sd : make_sets(n, pr)) {
@@ -626,28 +625,16 @@ size_t cost_table_bytes(int n)
     return cost_table_list(n).size() * ((size_t)tiles_per_state(n) * kCostRow + 256 * 8) * sizeof(double);
 }
 
-// Per-tile tables of one quadratic cost c0 + sum l_i z_i + sum_{i<j} b_ij z_i z_j (see
-// qq_problem::CostTab): the rows on the device from the device coefficient lists, the per-thread
-// constants (P(E) and l_Rj + sum_{q in E} b_q,Rj, with E the thread's lane and wave bits) on the host.
-// `ell` / `B` give the host coefficients; `*d_out` receives the one allocation.
+// Per-thread constants of the tables of one quadratic cost c0 + sum l_i z_i + sum_{i<j} b_ij z_i z_j
+// (see qq_problem::CostTab), [table][256][8]: P(E) and l_Rj + sum_{q in E} b_q,Rj, with E the thread's
+// lane and wave bits.
 template <typename BF>
-qq_status build_tables(int n, const std::vector<double> &ell, BF B, const double *d_ell, int np,
-                       const int32_t *d_pij, const double *d_pb, double c0, std::vector<qq_problem::CostTab> &tabs,
-                       double **d_out, hipStream_t stream)
+std::vector<double> table_constants(const std::vector<qq_problem::CostTab> &tabs, const std::vector<double> &ell, BF B)
 {
-    tabs = cost_table_list(n);
-    if (tabs.empty()) return QQ_OK;
-    const uint64_t T = tiles_per_state(n);
-    const size_t per = (size_t)T * kCostRow + 256 * 8;
-    if (hipMalloc((void **)d_out, per * tabs.size() * sizeof(double)) != hipSuccess)
-        return fail(QQ_E_NOMEM, "hipMalloc(%zu) for the cost tables failed", per * tabs.size() * sizeof(double));
     std::vector<double> thr(256 * 8 * tabs.size(), 0.0);
     for (size_t k = 0; k < tabs.size(); ++k) {
-        qq_problem::CostTab &tb = tabs[k];
-        tb.off = k * per;
+        const qq_problem::CostTab &tb = tabs[k];
         const int lq = tb.lane_q, rq = lq == tb.pos4 ? tb.pos8 : tb.pos4;
-        QQ_HIP(launch_cost_table(n, tb.high, tb.pos4, tb.pos8, lq, rq, T, d_ell, np, d_pij, d_pb, c0, *d_out + tb.off,
-                                 stream));
         const int eq[8] = {0, 1, 2, 3, lq, lq + 1, lq + 2, lq + 3};
         for (int t = 0; t < 256; ++t) {
             double P = 0.0;
@@ -667,33 +654,34 @@ qq_status build_tables(int n, const std::vector<double> &ell, BF B, const double
             }
         }
     }
-    for (size_t k = 0; k < tabs.size(); ++k)
-        QQ_HIP(hipMemcpyAsync(*d_out + tabs[k].off + (size_t)T * kCostRow, &thr[k * 256 * 8], 256 * 8 * sizeof(double),
-                              hipMemcpyHostToDevice, stream));
-    QQ_HIP(hipStreamSynchronize(stream));
+    return thr;
+}
+
+// The tables' rows, computed on the device into `buf`; d_thr holds the per-thread constants.
+qq_status build_tables(int device, int n, const double *d_ell, int np, const int32_t *d_pij, const double *d_pb,
+                       double c0, std::vector<qq_problem::CostTab> &tabs, DevBuf &buf, const double *d_thr,
+                       hipStream_t stream)
+{
+    if (tabs.empty()) return QQ_OK;
+    const uint64_t T = tiles_per_state(n);
+    const size_t per = (size_t)T * kCostRow, need = per * tabs.size() * sizeof(double);
+    if (buf.get(device, need) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) for the cost tables failed", need);
+    for (size_t k = 0; k < tabs.size(); ++k) {
+        qq_problem::CostTab &tb = tabs[k];
+        double *rows = static_cast<double *>(buf.p) + k * per;
+        tb.rows = rows;
+        tb.thr = d_thr + k * 256 * 8;
+        const int lq = tb.lane_q, rq = lq == tb.pos4 ? tb.pos8 : tb.pos4;
+        QQ_HIP(launch_cost_table(n, tb.high, tb.pos4, tb.pos8, lq, rq, T, d_ell, np, d_pij, d_pb, c0, rows, stream));
+    }
     return QQ_OK;
 }
 
-// The cost tables of the whole cost (at problem creation).
-qq_status build_cost_tables(qq_problem *pb, hipStream_t stream)
-{
-    const int n = pb->n;
-    auto B = [&](int i, int j) { return i < j ? pb->b[(size_t)i * n + j] : pb->b[(size_t)j * n + i]; };
-    return build_tables(n, pb->ell, B, pb->d_ell, (int)pb->pair_b.size(), pb->d_pair_ij, pb->d_pair_b, pb->c0,
-                        pb->ctabs, &pb->d_ctab, stream);
-}
-
-const double *find_table(const std::vector<qq_problem::CostTab> &tabs, const double *base, const SetDesc &sd,
-                         int lane_q)
+const qq_problem::CostTab *find_table(const std::vector<qq_problem::CostTab> &tabs, const SetDesc &sd, int lane_q)
 {
     for (const auto &t : tabs)
-        if (t.high == sd.high && t.pos4 == sd.pos4 && t.pos8 == sd.pos8 && t.lane_q == lane_q) return base + t.off;
+        if (t.high == sd.high && t.pos4 == sd.pos4 && t.pos8 == sd.pos8 && t.lane_q == lane_q) return &t;
     return nullptr;
-}
-
-const double *find_cost_table(const qq_problem *pb, const SetDesc &sd, int lane_q)
-{
-    return find_table(pb->ctabs, pb->d_ctab, sd, lane_q);
 }
 
 // Run every pass of a plan and the final reduction.  `ws` is device memory laid out by `L`.
@@ -780,14 +768,17 @@ qq_status run_plan(qq_problem *pb, const Plan &plan, const Layout &L, int p, int
             fp.part_cq_runs = std::max(1, pb->n - 3);
             fp.shift = pb->alpha;
             // the table of the layout the pass reads the cost in: lanes at pos4 for the first pass, at pos8 else
-            fp.ctab = find_cost_table(pb, sd, pp.fkind == FK_FIRST ? sd.pos4 : sd.pos8);
-            if (!fp.ctab) return fail(QQ_E_DEVICE, "no cost table for the set at qubits %d / %d", sd.pos4, sd.pos8);
-            fp.cthr = fp.ctab + (size_t)T * kCostRow;
+            const int lane_q = pp.fkind == FK_FIRST ? sd.pos4 : sd.pos8;
+            const auto *ct = find_table(pb->ctabs, sd, lane_q);
+            if (!ct) return fail(QQ_E_DEVICE, "no cost table for the set at qubits %d / %d", sd.pos4, sd.pos8);
+            fp.ctab = ct->rows;
+            fp.cthr = ct->thr;
             fp.xtab = fp.xthr = nullptr;
             if (fp.part) {
-                fp.xtab = find_table(pb->xtabs, pb->d_xtab, sd, pp.fkind == FK_FIRST ? sd.pos4 : sd.pos8);
-                if (!fp.xtab) return fail(QQ_E_DEVICE, "no cross table for the set at qubits %d / %d", sd.pos4, sd.pos8);
-                fp.xthr = fp.xtab + (size_t)T * kCostRow;
+                const auto *xt = find_table(pb->xtabs, sd, lane_q);
+                if (!xt) return fail(QQ_E_DEVICE, "no cross table for the set at qubits %d / %d", sd.pos4, sd.pos8);
+                fp.xtab = xt->rows;
+                fp.xthr = xt->thr;
             }
             QQ_HIP(launch_fast_pass(pp.fkind, sd.high != 0, pb->diag_type, fp, stream));
         } else {
@@ -905,7 +896,7 @@ struct qq_graph {
     Layout L;
     double lr = 0.01, beta1 = 0.9, beta2 = 0.999, eps = 1e-8;
     double *x = nullptr;  // caller's device parameters [B][2p]
-    void *mem = nullptr;  // workspace, moments, outputs, counter (one allocation)
+    DevBuf mem;  // workspace, moments, outputs, counter (one allocation)
     char *ws = nullptr;
     double *m = nullptr, *v = nullptr, *energy = nullptr, *grad = nullptr, *hist = nullptr;
     int *step = nullptr;
@@ -920,7 +911,9 @@ struct qq_graph {
         if (exec) (void)hipGraphExecDestroy(exec);
         if (graph) (void)hipGraphDestroy(graph);
         if (cap) (void)hipStreamDestroy(cap);
-        if (mem) (void)hipFree(mem);
+        // replays on the caller's streams may still run
+        if (mem.p && hipDeviceSynchronize() == hipSuccess) mem.done();
+        mem.release();
     }
 };
 
@@ -1249,9 +1242,10 @@ qq_status plan_many(int count, qq_problem *const *pbs, const int *p, const int *
                     P.store_psi = (pp.flags & PF_STORE_PSI) ? 1 : 0;
                     P.slot_base = slot_base;
                     P.nslots = (int)pp.slot_out.size();
-                    P.ctab = find_cost_table(pb, sd, pp.fkind == FK_FIRST ? sd.pos4 : sd.pos8);
-                    if (!P.ctab) return fail(QQ_E_DEVICE, "no cost table for the set at qubits %d / %d", sd.pos4, sd.pos8);
-                    P.cthr = P.ctab + (size_t)I.tiles * kCostRow;
+                    const auto *ct = find_table(pb->ctabs, sd, pp.fkind == FK_FIRST ? sd.pos4 : sd.pos8);
+                    if (!ct) return fail(QQ_E_DEVICE, "no cost table for the set at qubits %d / %d", sd.pos4, sd.pos8);
+                    P.ctab = ct->rows;
+                    P.cthr = ct->thr;
                     slot_base += P.nslots;
                     for (int o : pp.slot_out) G.slot_out.push_back((uint16_t)o);
                     G.pass.push_back(P);
@@ -1472,7 +1466,7 @@ qq_status recompute_c128(std::vector<C128Job> &jobs, int flags, void *stream_)
     const size_t need = (size_t)ns * wsa + (nx + nout) * sizeof(double);
     if (qq_status st = check_device_fits(device, need, "the complex128 recomputation"); st != QQ_OK) return st;
     DevBuf ws, buf;
-    if (hipMalloc(&ws.p, (size_t)ns * wsa) != hipSuccess || hipMalloc(&buf.p, (nx + nout) * sizeof(double)) != hipSuccess)
+    if (ws.get(device, (size_t)ns * wsa) != hipSuccess || buf.get(device, (nx + nout) * sizeof(double)) != hipSuccess)
         return fail(QQ_E_NOMEM, "hipMalloc of %zu bytes for the complex128 recomputation failed", need);
     double *d_x = static_cast<double *>(buf.p), *d_out = d_x + nx;
     std::vector<double> x(nx), h(nout);
@@ -1512,6 +1506,8 @@ qq_status recompute_c128(std::vector<C128Job> &jobs, int flags, void *stream_)
     for (hipStream_t sk : side.s) QQ_HIP(hipStreamSynchronize(sk));
     QQ_HIP(hipMemcpyAsync(h.data(), d_out, nout * sizeof(double), hipMemcpyDeviceToHost, stream));
     QQ_HIP(hipStreamSynchronize(stream));
+    ws.done();
+    buf.done();
     oo = 0;
     for (C128Job &j : jobs) {
         if (j.sets.empty()) continue;
@@ -1648,52 +1644,68 @@ qq_status qq_problem_create(int n, const double *H, const double *f, double c0, 
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     QQ_HIP(hipSetDevice(device));
     const int np = (int)pb->pair_b.size();
-    if (hipMalloc(&pb->d_diag, dbytes) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) for the diagonal failed", dbytes);
-    QQ_HIP(hipMalloc((void **)&pb->d_ell, sizeof(double) * n));
-    QQ_HIP(hipMalloc((void **)&pb->d_ell_i, sizeof(int32_t) * n));
-    QQ_HIP(hipMalloc((void **)&pb->d_pair_ij, sizeof(int32_t) * std::max(2, 2 * np)));
-    QQ_HIP(hipMalloc((void **)&pb->d_pair_b, sizeof(double) * std::max(1, np)));
-    QQ_HIP(hipMalloc((void **)&pb->d_pair_bi, sizeof(int32_t) * std::max(1, np)));
-    {
-        std::vector<double> regq(16 * (size_t)std::max(1, n - 3), 0.0);
-        for (int q = 0; q + 4 <= n; ++q)
-            for (int r = 1; r < 16; ++r) {
-                const int j = __builtin_ctz(r);
-                double sum = 0.0;
-                for (int k = j + 1; k < 4; ++k)
-                    if ((r >> k) & 1) sum += pb->b[(size_t)(q + j) * n + (q + k)];
-                regq[16 * (size_t)q + r] = sum;
-            }
-        QQ_HIP(hipMalloc((void **)&pb->d_regq, sizeof(double) * regq.size()));
-        QQ_HIP(hipMemcpy(pb->d_regq, regq.data(), sizeof(double) * regq.size(), hipMemcpyHostToDevice));
-    }
-    QQ_HIP(hipMemcpyAsync(pb->d_ell, pb->ell.data(), sizeof(double) * n, hipMemcpyHostToDevice, stream));
-    QQ_HIP(hipMemcpyAsync(pb->d_ell_i, pb->ell_i.data(), sizeof(int32_t) * n, hipMemcpyHostToDevice, stream));
-    if (np) {
-        QQ_HIP(hipMemcpyAsync(pb->d_pair_ij, pb->pair_ij.data(), sizeof(int32_t) * 2 * np, hipMemcpyHostToDevice, stream));
-        QQ_HIP(hipMemcpyAsync(pb->d_pair_b, pb->pair_b.data(), sizeof(double) * np, hipMemcpyHostToDevice, stream));
-        QQ_HIP(hipMemcpyAsync(pb->d_pair_bi, pb->pair_bi.data(), sizeof(int32_t) * np, hipMemcpyHostToDevice, stream));
-    }
+    if (pb->diag_buf.get(device, dbytes) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) for the diagonal failed", dbytes);
+    pb->d_diag = pb->diag_buf.p;
+    pb->counted = true;
+    pool_problem_added(device);
+    // the coefficient lists, the register-run sums and the tables' per-thread constants: one block, one copy
+    std::vector<double> regq(16 * (size_t)std::max(1, n - 3), 0.0);
+    for (int q = 0; q + 4 <= n; ++q)
+        for (int r = 1; r < 16; ++r) {
+            const int j = __builtin_ctz(r);
+            double sum = 0.0;
+            for (int k = j + 1; k < 4; ++k)
+                if ((r >> k) & 1) sum += pb->b[(size_t)(q + j) * n + (q + k)];
+            regq[16 * (size_t)q + r] = sum;
+        }
+    pb->ctabs = cost_table_list(n);
+    const std::vector<double> thr = table_constants(pb->ctabs, pb->ell, [&](int i, int j) {
+        return i < j ? pb->b[(size_t)i * n + j] : pb->b[(size_t)j * n + i];
+    });
+    std::vector<char> host;
+    auto put = [&](const void *src, size_t bytes) {
+        const size_t at = align_up(host.size());
+        host.resize(at + std::max<size_t>(bytes, 16));
+        if (bytes) std::memcpy(host.data() + at, src, bytes);
+        return at;
+    };
+    const size_t o_ell = put(pb->ell.data(), sizeof(double) * n), o_elli = put(pb->ell_i.data(), sizeof(int32_t) * n),
+                 o_pij = put(pb->pair_ij.data(), sizeof(int32_t) * 2 * np), o_pb = put(pb->pair_b.data(), sizeof(double) * np),
+                 o_pbi = put(pb->pair_bi.data(), sizeof(int32_t) * np), o_regq = put(regq.data(), sizeof(double) * regq.size()),
+                 o_thr = put(thr.data(), sizeof(double) * thr.size());
+    QQ_HIP(pb->coef_buf.get(device, host.size()));
+    char *coef = static_cast<char *>(pb->coef_buf.p);
+    QQ_HIP(hipMemcpyAsync(coef, host.data(), host.size(), hipMemcpyHostToDevice, stream));
+    pb->d_ell = reinterpret_cast<double *>(coef + o_ell);
+    pb->d_ell_i = reinterpret_cast<int32_t *>(coef + o_elli);
+    pb->d_pair_ij = reinterpret_cast<int32_t *>(coef + o_pij);
+    pb->d_pair_b = reinterpret_cast<double *>(coef + o_pb);
+    pb->d_pair_bi = reinterpret_cast<int32_t *>(coef + o_pbi);
+    pb->d_regq = reinterpret_cast<double *>(coef + o_regq);
     QQ_HIP(prof_aux(5, n, diag_bytes_of(pb->diag_type), (double)dbytes, stream, [&]() {
         return launch_cost_diag(n, pb->diag_type, pb->d_ell, pb->d_ell_i, np, pb->d_pair_ij, pb->d_pair_b,
                                 pb->d_pair_bi, c0, pb->c0_i, pb->d_diag, pb->dim, stream);
     }));
-    if (qq_status st = build_cost_tables(pb, stream); st != QQ_OK) return st;
+    if (qq_status st = build_tables(device, n, pb->d_ell, np, pb->d_pair_ij, pb->d_pair_b, c0, pb->ctabs, pb->ctab_buf,
+                                    reinterpret_cast<const double *>(coef + o_thr), stream);
+        st != QQ_OK)
+        return st;
 
     // min / argmin / max of C
     const int nblk = (int)std::min<uint64_t>(1024, (pb->dim + 255) / 256);
     DevBuf part;
-    QQ_HIP(hipMalloc(&part.p, (size_t)nblk * (2 * sizeof(double) + sizeof(uint64_t))));
+    std::vector<double> hp(3 * (size_t)nblk);
+    QQ_HIP(part.get(device, hp.size() * sizeof(double)));
     double *d_part = static_cast<double *>(part.p);
     uint64_t *d_idx = reinterpret_cast<uint64_t *>(d_part + 2 * nblk);
     QQ_HIP(prof_aux(6, n, diag_bytes_of(pb->diag_type), (double)dbytes, stream, [&]() {
         return launch_minmax(pb->d_diag, pb->diag_type, pb->dim, d_part, d_idx, nblk, stream);
     }));
-    std::vector<double> hp(2 * nblk);
-    std::vector<uint64_t> hi(nblk);
-    QQ_HIP(hipMemcpyAsync(hp.data(), d_part, sizeof(double) * 2 * nblk, hipMemcpyDeviceToHost, stream));
-    QQ_HIP(hipMemcpyAsync(hi.data(), d_idx, sizeof(uint64_t) * nblk, hipMemcpyDeviceToHost, stream));
+    QQ_HIP(hipMemcpyAsync(hp.data(), d_part, hp.size() * sizeof(double), hipMemcpyDeviceToHost, stream));
     QQ_HIP(hipStreamSynchronize(stream));
+    part.done();
+    std::vector<uint64_t> hi(nblk);
+    std::memcpy(hi.data(), hp.data() + 2 * nblk, sizeof(uint64_t) * nblk);
     double mn = INFINITY, mx = -INFINITY;
     uint64_t mi = ~0ull;
     for (int k = 0; k < nblk; ++k) {
@@ -1774,10 +1786,11 @@ qq_status qq_cost_diagonal(const qq_problem *pb, void *out, int flags, void *str
         return QQ_OK;
     }
     DevBuf tmp;
-    if (hipMalloc(&tmp.p, ob) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) failed", ob);
+    if (tmp.get(pb->device, ob) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) failed", ob);
     QQ_HIP(launch_widen_diag(pb->d_diag, pb->diag_type, pb->dim, tmp.p, stream));
     QQ_HIP(hipMemcpyAsync(out, tmp.p, ob, hipMemcpyDeviceToHost, stream));
     QQ_HIP(hipStreamSynchronize(stream));
+    tmp.done();
     return QQ_OK;
 }
 
@@ -1836,10 +1849,11 @@ qq_status qq_set_allocation(qq_problem *pb, int M, const int32_t *qpu_of_var, co
         return st;
     QQ_HIP(hipSetDevice(pb->device));
     // release a previous allocation
-    void *olds[] = {pb->d_qpu, pb->d_tables, pb->d_cross, pb->d_part, pb->d_part_cq, pb->d_xtab};
+    void *olds[] = {pb->d_qpu, pb->d_tables, pb->d_cross, pb->d_part, pb->d_part_cq};
     for (void *q : olds)
         if (q) QQ_HIP(hipFree(q));
-    pb->d_xtab = nullptr;
+    pb->xtab_buf.release();
+    pb->xthr_buf.release();
     pb->xtabs.clear();
     pb->d_part_cq = nullptr;
     pb->d_qpu = nullptr;
@@ -1881,13 +1895,13 @@ qq_status qq_set_allocation(qq_problem *pb, int M, const int32_t *qpu_of_var, co
     {
         const int nx = (int)xb.size();
         DevBuf zero_ell, zero_elli, dij, db, dbi;
-        QQ_HIP(hipMalloc(&zero_ell.p, sizeof(double) * n));
-        QQ_HIP(hipMalloc(&zero_elli.p, sizeof(int32_t) * n));
+        QQ_HIP(zero_ell.get(pb->device, sizeof(double) * n));
+        QQ_HIP(zero_elli.get(pb->device, sizeof(int32_t) * n));
         QQ_HIP(hipMemset(zero_ell.p, 0, sizeof(double) * n));
         QQ_HIP(hipMemset(zero_elli.p, 0, sizeof(int32_t) * n));
-        QQ_HIP(hipMalloc(&dij.p, sizeof(int32_t) * std::max(2, 2 * nx)));
-        QQ_HIP(hipMalloc(&db.p, sizeof(double) * std::max(1, nx)));
-        QQ_HIP(hipMalloc(&dbi.p, sizeof(int32_t) * std::max(1, nx)));
+        QQ_HIP(dij.get(pb->device, sizeof(int32_t) * std::max(2, 2 * nx)));
+        QQ_HIP(db.get(pb->device, sizeof(double) * std::max(1, nx)));
+        QQ_HIP(dbi.get(pb->device, sizeof(int32_t) * std::max(1, nx)));
         if (nx) {
             QQ_HIP(hipMemcpy(dij.p, xij.data(), sizeof(int32_t) * 2 * nx, hipMemcpyHostToDevice));
             QQ_HIP(hipMemcpy(db.p, xb.data(), sizeof(double) * nx, hipMemcpyHostToDevice));
@@ -1902,12 +1916,19 @@ qq_status qq_set_allocation(qq_problem *pb, int M, const int32_t *qpu_of_var, co
             if (qpu_of_var[i] == qpu_of_var[j]) return 0.0;
             return i < j ? pb->b[(size_t)i * n + j] : pb->b[(size_t)j * n + i];
         };
-        if (qq_status st = build_tables(n, zeros, BX, static_cast<double *>(zero_ell.p), nx,
+        pb->xtabs = cost_table_list(n);
+        const std::vector<double> thr = table_constants(pb->xtabs, zeros, BX);
+        if (!thr.empty()) {
+            QQ_HIP(pb->xthr_buf.get(pb->device, thr.size() * sizeof(double)));
+            QQ_HIP(hipMemcpy(pb->xthr_buf.p, thr.data(), thr.size() * sizeof(double), hipMemcpyHostToDevice));
+        }
+        if (qq_status st = build_tables(pb->device, n, static_cast<double *>(zero_ell.p), nx,
                                         static_cast<int32_t *>(dij.p), static_cast<double *>(db.p), 0.0, pb->xtabs,
-                                        &pb->d_xtab, stream);
+                                        pb->xtab_buf, static_cast<const double *>(pb->xthr_buf.p), stream);
             st != QQ_OK)
             return st;
         QQ_HIP(hipDeviceSynchronize());
+        for (DevBuf *q : {&zero_ell, &zero_elli, &dij, &db, &dbi}) q->done();
     }
     pb->num_qpus = M;
     pb->qpu.assign(qpu_of_var, qpu_of_var + n);
@@ -1944,7 +1965,7 @@ static qq_status evaluate_impl(qq_problem *pb, int p, int batch, const double *p
     char *ws = static_cast<char *>(workspace);
     if (!ws) {
         if (qq_status st = check_device_fits(pb->device, L.total, "the workspace"); st != QQ_OK) return st;
-        if (hipMalloc(&own.p, L.total) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) for the workspace failed", L.total);
+        if (own.get(pb->device, L.total) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) for the workspace failed", L.total);
         ws = static_cast<char *>(own.p);
     } else if (ws_bytes < L.total) {
         return fail(QQ_E_WORKSPACE, "workspace of %zu bytes, need %zu", ws_bytes, L.total);
@@ -1961,11 +1982,13 @@ static qq_status evaluate_impl(qq_problem *pb, int p, int batch, const double *p
             QQ_HIP(hipMemcpy2DAsync(grad_out, 2 * p * sizeof(double), d_out + 1, nout * sizeof(double),
                                     2 * p * sizeof(double), batch, hipMemcpyDeviceToDevice, stream));
         if (own.p) QQ_HIP(hipStreamSynchronize(stream));
+        own.done();
         return QQ_OK;
     }
     std::vector<double> h((size_t)batch * nout);
     QQ_HIP(hipMemcpyAsync(h.data(), d_out, h.size() * sizeof(double), hipMemcpyDeviceToHost, stream));
     QQ_HIP(hipStreamSynchronize(stream));
+    own.done();
     for (int b = 0; b < batch; ++b) {
         energy_out[b] = h[(size_t)b * nout];
         if (grad)
@@ -2029,7 +2052,7 @@ static qq_status state_into(qq_problem *pb, int p, const double *params, int fla
     L = layout_for(pb, p, 1, f, plan);
     QQ_HIP(hipSetDevice(pb->device));
     if (qq_status st = check_device_fits(pb->device, L.total, "the state"); st != QQ_OK) return st;
-    if (hipMalloc(&own.p, L.total) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) failed", L.total);
+    if (own.get(pb->device, L.total) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) failed", L.total);
     QQ_HIP(poison(own.p, L.total, stream));
     return eval_core(pb, p, 1, params, f, plan, L, static_cast<char *>(own.p), stream);
 }
@@ -2046,6 +2069,7 @@ qq_status qq_state(qq_problem *pb, int p, const double *params, int flags, void 
     QQ_HIP(hipMemcpyAsync(psi_out, static_cast<char *>(own.p) + L.psi, bytes,
                           (flags & QQ_OUT_ON_DEVICE) ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost, stream));
     QQ_HIP(hipStreamSynchronize(stream));
+    own.done();
     return QQ_OK;
 }
 
@@ -2084,7 +2108,7 @@ qq_status qq_telegate_state(qq_problem *pb, int p, const double *params, const d
     QQ_HIP(hipSetDevice(pb->device));
     if (qq_status st = check_device_fits(pb->device, total, "the trajectory state"); st != QQ_OK) return st;
     DevBuf buf;
-    if (hipMalloc(&buf.p, total) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) failed", total);
+    if (buf.get(pb->device, total) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) failed", total);
     char *b = static_cast<char *>(buf.p);
     double2 *psi = reinterpret_cast<double2 *>(b);
     double *partial = reinterpret_cast<double *>(b + o_part);
@@ -2130,6 +2154,7 @@ qq_status qq_telegate_state(qq_problem *pb, int p, const double *params, const d
     if (outcomes_out && nmeas > 0)
         QQ_HIP(hipMemcpyAsync(outcomes_out, outcome, (size_t)nmeas * 4, hipMemcpyDeviceToHost, stream));
     QQ_HIP(hipStreamSynchronize(stream));
+    buf.done();
     if (remote_out) *remote_out = nremote;
     return QQ_OK;
 }
@@ -2158,7 +2183,7 @@ qq_status qq_sample(qq_problem *pb, int p, const double *params, int flags, int6
                  o_out = o_u + (dev_in ? 0 : align_up((size_t)shots * sizeof(double))),
                  total = o_out + (dev_out ? 0 : align_up((size_t)shots * sizeof(uint64_t)));
     DevBuf buf;
-    if (hipMalloc(&buf.p, total) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) for the shots failed", total);
+    if (buf.get(pb->device, total) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) for the shots failed", total);
     char *b = static_cast<char *>(buf.p);
     double *d_mass = reinterpret_cast<double *>(b), *d_start = reinterpret_cast<double *>(b + o_start);
     const double *d_u = dev_in ? uniforms : reinterpret_cast<const double *>(b + o_u);
@@ -2181,6 +2206,8 @@ qq_status qq_sample(qq_problem *pb, int p, const double *params, int flags, int6
     if (!dev_out)
         QQ_HIP(hipMemcpyAsync(indices_out, d_out, (size_t)shots * sizeof(uint64_t), hipMemcpyDeviceToHost, stream));
     QQ_HIP(hipStreamSynchronize(stream));
+    own.done();
+    buf.done();
     return QQ_OK;
 }
 
@@ -2212,7 +2239,7 @@ qq_status qq_sample_stats(qq_problem *pb, int64_t shots, const uint64_t *indices
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     QQ_HIP(hipSetDevice(pb->device));
     DevBuf buf;
-    if (hipMalloc(&buf.p, (size_t)m * 16) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc failed");
+    if (buf.get(pb->device, (size_t)m * 16) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc failed");
     uint64_t *d_idx = static_cast<uint64_t *>(buf.p);
     double *d_cost = reinterpret_cast<double *>(d_idx + m);
     std::vector<double> cost(m);
@@ -2220,6 +2247,7 @@ qq_status qq_sample_stats(qq_problem *pb, int64_t shots, const uint64_t *indices
     QQ_HIP(launch_gather_cost(pb->d_diag, pb->diag_type, d_idx, m, d_cost, stream));
     QQ_HIP(hipMemcpyAsync(cost.data(), d_cost, (size_t)m * 8, hipMemcpyDeviceToHost, stream));
     QQ_HIP(hipStreamSynchronize(stream));
+    buf.done();
 
     std::memset(out, 0, sizeof *out);
     const double S = (double)shots;
@@ -2282,15 +2310,18 @@ qq_status qq_probabilities(qq_problem *pb, int p, const double *params, int flag
             return launch_probabilities(psi, flags & QQ_C128, pb->dim, prob_out, stream);
         }));
         QQ_HIP(hipStreamSynchronize(stream));
+        own.done();
         return QQ_OK;
     }
     DevBuf tmp;
-    if (hipMalloc(&tmp.p, (size_t)pb->dim * sizeof(double)) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc failed");
+    if (tmp.get(pb->device, (size_t)pb->dim * sizeof(double)) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc failed");
     QQ_HIP(prof_aux(7, pb->n, 0, (double)pb->dim * (((flags & QQ_C128) ? 16 : 8) + 8), stream, [&]() {
         return launch_probabilities(psi, flags & QQ_C128, pb->dim, static_cast<double *>(tmp.p), stream);
     }));
     QQ_HIP(hipMemcpyAsync(prob_out, tmp.p, (size_t)pb->dim * sizeof(double), hipMemcpyDeviceToHost, stream));
     QQ_HIP(hipStreamSynchronize(stream));
+    own.done();
+    tmp.done();
     return QQ_OK;
 }
 
@@ -2309,7 +2340,7 @@ qq_status qq_topk(qq_problem *pb, int p, const double *params, int flags, int k,
     const int nblocks = (int)std::min<uint64_t>(1024, (pb->dim + 255) / 256);
     DevBuf scratch;
     const size_t sb = (size_t)nblocks * k * 16 + (size_t)k * 24 + 256;
-    if (hipMalloc(&scratch.p, sb) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc failed");
+    if (scratch.get(pb->device, sb) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc failed");
     char *sc = static_cast<char *>(scratch.p);
     uint64_t *d_idx = reinterpret_cast<uint64_t *>(sc + (size_t)nblocks * k * 16);
     double *d_prob = reinterpret_cast<double *>(d_idx + k);
@@ -2318,15 +2349,14 @@ qq_status qq_topk(qq_problem *pb, int p, const double *params, int flags, int k,
         return launch_topk(psi, flags & QQ_C128, pb->dim, k, pb->d_diag, pb->diag_type, d_idx, d_prob, d_cost, sc,
                            nblocks, stream);
     }));
-    std::vector<uint64_t> hi(k);
-    std::vector<double> hp(k), hc(k);
-    QQ_HIP(hipMemcpyAsync(hi.data(), d_idx, sizeof(uint64_t) * k, hipMemcpyDeviceToHost, stream));
-    QQ_HIP(hipMemcpyAsync(hp.data(), d_prob, sizeof(double) * k, hipMemcpyDeviceToHost, stream));
-    QQ_HIP(hipMemcpyAsync(hc.data(), d_cost, sizeof(double) * k, hipMemcpyDeviceToHost, stream));
+    std::vector<uint64_t> hi(3 * (size_t)k);  // indices, probabilities, costs
+    QQ_HIP(hipMemcpyAsync(hi.data(), d_idx, hi.size() * sizeof(uint64_t), hipMemcpyDeviceToHost, stream));
     QQ_HIP(hipStreamSynchronize(stream));
-    std::copy(hi.begin(), hi.end(), idx_out);
-    std::copy(hp.begin(), hp.end(), prob_out);
-    if (cost_out) std::copy(hc.begin(), hc.end(), cost_out);
+    own.done();
+    scratch.done();
+    std::memcpy(idx_out, hi.data(), sizeof(uint64_t) * k);
+    std::memcpy(prob_out, hi.data() + k, sizeof(double) * k);
+    if (cost_out) std::memcpy(cost_out, hi.data() + 2 * k, sizeof(double) * k);
     return QQ_OK;
 }
 
@@ -2369,7 +2399,7 @@ static qq_status evaluate_many_impl(int count, qq_problem *const *problems, cons
     char *ws = static_cast<char *>(workspace);
     if (!ws) {
         if (qq_status st = check_device_fits(device, M.total, "the workspace"); st != QQ_OK) return st;
-        if (hipMalloc(&own.p, M.total) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) for the workspace failed", M.total);
+        if (own.get(device, M.total) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) for the workspace failed", M.total);
         ws = static_cast<char *>(own.p);
     } else if (ws_bytes < M.total) {
         return fail(QQ_E_WORKSPACE, "workspace of %zu bytes, need %zu", ws_bytes, M.total);
@@ -2480,6 +2510,7 @@ static qq_status evaluate_many_impl(int count, qq_problem *const *problems, cons
         QQ_HIP(hipMemcpyAsync(h.data(), ws + M.out, nout * sizeof(double), hipMemcpyDeviceToHost, stream));
     }
     QQ_HIP(hipStreamSynchronize(stream));
+    own.done();
     for (uint32_t f : flags_h)
         if (f) return fail(QQ_E_DEVICE, "persistent launch: a dependency wait exceeded %.0f ms; results are invalid", wait_ms);
     if (!(flags & QQ_OUT_ON_DEVICE)) {
@@ -2621,8 +2652,8 @@ qq_status qq_graph_create(qq_problem *pb, int p, int batch, int flags, const dou
                  o_s = o_h + align_up((size_t)std::max(1, history) * batch * 8), total = o_s + 256;
     QQ_HIP(hipSetDevice(g->device));
     if (qq_status st = check_device_fits(g->device, total, "the optimiser workspace"); st != QQ_OK) return st;
-    if (hipMalloc(&g->mem, total) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) failed", total);
-    char *base = static_cast<char *>(g->mem);
+    if (g->mem.get(g->device, total) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) failed", total);
+    char *base = static_cast<char *>(g->mem.p);
     g->ws = base;
     g->m = reinterpret_cast<double *>(base + o_m);
     g->v = reinterpret_cast<double *>(base + o_v);
@@ -2804,9 +2835,9 @@ qq_status qq_autotune(qq_problem *pb, int p, int batch, int flags, const char *c
     for (int G : g_candidates(G0 * 2)) need = std::max(need, make_layout(pb, p, batch, flags, plan0, G).total);
     if (qq_status st = check_device_fits(pb->device, need, "the tuning workspace"); st != QQ_OK) return st;
     DevBuf ws, dx;
-    if (hipMalloc(&ws.p, need) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) for tuning failed", need);
+    if (ws.get(pb->device, need) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) for tuning failed", need);
     const std::vector<double> x = tune_params((size_t)batch * 2 * p, 0x5eed + (uint64_t)pb->n * 131 + p);
-    QQ_HIP(hipMalloc(&dx.p, x.size() * sizeof(double)));
+    QQ_HIP(dx.get(pb->device, x.size() * sizeof(double)));
     QQ_HIP(hipMemcpy(dx.p, x.data(), x.size() * sizeof(double), hipMemcpyHostToDevice));
     const int eflags = flags | QQ_PARAMS_ON_DEVICE;
     double best = INFINITY;
@@ -2896,8 +2927,8 @@ qq_status qq_autotune_many(int count, qq_problem *const *problems, const int *p,
         ne += (size_t)batch[i];
     }
     DevBuf dparams, dout;
-    QQ_HIP(hipMalloc(&dparams.p, np * sizeof(double)));
-    QQ_HIP(hipMalloc(&dout.p, (ne + np) * sizeof(double)));
+    QQ_HIP(dparams.get(device, np * sizeof(double)));
+    QQ_HIP(dout.get(device, (ne + np) * sizeof(double)));
     std::vector<const double *> pp(count);
     std::vector<double *> ep(count), gp(count);
     {
@@ -2924,7 +2955,7 @@ qq_status qq_autotune_many(int count, qq_problem *const *problems, const int *p,
     }
     if (qq_status st = check_device_fits(device, need, "the tuning workspace"); st != QQ_OK) return st;
     DevBuf ws;
-    if (hipMalloc(&ws.p, need) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) for tuning failed", need);
+    if (ws.get(device, need) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) for tuning failed", need);
     double best = INFINITY;
     qq_many_options bopt{16, 0, 0.0};
     for (const auto &c : cands) {
@@ -2993,7 +3024,7 @@ qq_status qq_evaluate_plain(qq_problem *pb, int p, const double *params, int fla
     QQ_HIP(hipSetDevice(pb->device));
     if (qq_status st = check_device_fits(pb->device, total, "the plain-path states"); st != QQ_OK) return st;
     DevBuf own;
-    if (hipMalloc(&own.p, total) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) failed", total);
+    if (own.get(pb->device, total) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) failed", total);
     char *ws = static_cast<char *>(own.p);
     PlainArgs a;
     a.n = pb->n;
@@ -3013,6 +3044,7 @@ qq_status qq_evaluate_plain(qq_problem *pb, int p, const double *params, int fla
     std::vector<double> h(1 + 2 * p);
     QQ_HIP(hipMemcpyAsync(h.data(), a.result, sizeof(double) * h.size(), hipMemcpyDeviceToHost, stream));
     QQ_HIP(hipStreamSynchronize(stream));
+    own.done();
     energy_out[0] = h[0];
     if (grad)
         for (int j = 0; j < 2 * p; ++j) grad_out[j] = h[1 + j];

@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "qq_internal.h"
+#include "qq_pool.h"
 
 using namespace qq;
 
@@ -48,14 +49,6 @@ int rank_first(const std::vector<double> &e)
     }
     return best;
 }
-
-struct DevMem {
-    void *p = nullptr;
-    ~DevMem()
-    {
-        if (p) (void)hipFree(p);
-    }
-};
 
 struct Graph {
     qq_graph *g = nullptr;
@@ -113,8 +106,8 @@ extern "C" qq_status qq_optimize(qq_problem *pb, const qq_optimize_options *o, c
         for (int j = 0; j < R; ++j, ++k, rp += 2 * p) std::memcpy(&x[(size_t)k * 2 * p], rp, sizeof(double) * 2 * p);
 
         // all starts of the depth step together: one graph-captured Adam step per iteration
-        DevMem dx;
-        if (hipMalloc(&dx.p, np * sizeof(double)) != hipSuccess)
+        DevBuf dx;
+        if (dx.get(problem_device(pb), np * sizeof(double)) != hipSuccess)
             return fail_msg(QQ_E_NOMEM, "hipMalloc of %d x %d parameters failed", S, 2 * p);
         if (hipMemcpyAsync(dx.p, x.data(), np * sizeof(double), hipMemcpyHostToDevice, stream) != hipSuccess)
             return fail_msg(QQ_E_DEVICE, "copying the starting points failed");
@@ -130,6 +123,7 @@ extern "C" qq_status qq_optimize(qq_problem *pb, const qq_optimize_options *o, c
         if (hipMemcpyAsync(x.data(), dx.p, np * sizeof(double), hipMemcpyDeviceToHost, stream) != hipSuccess ||
             hipStreamSynchronize(stream) != hipSuccess)
             return fail_msg(QQ_E_DEVICE, "copying the final parameters failed");
+        dx.done();
 
         // the exact energy at every start's final parameter vector ranks the starts
         std::vector<double> e(S);
