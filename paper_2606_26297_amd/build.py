@@ -19,7 +19,7 @@ CXX = os.environ.get("QQ_HOST_CXX", "/opt/rocm/llvm/bin/clang++")
 HOST = ["-x", "c++", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include"]
 ARCH = "gfx950"
 
-HIP_SOURCES = ["qq_kernels.hip", "qq_fast.hip", "qq_many.hip", "qq_optim.hip", "qq_plain.hip", "qq_sample.hip",
+HIP_SOURCES = ["qq_kernels.hip", "qq_fast.hip", "qq_fast128.hip", "qq_many.hip", "qq_optim.hip", "qq_plain.hip", "qq_sample.hip",
                "qq_telegate.hip", "qq_static.hip"]
 CPP_SOURCES = ["qq_api.cpp", "qq_driver.cpp", "qq_alloc.cpp", "qq_pool.cpp"]
 

@@ -475,6 +475,13 @@ int choose_G(int n, int B)
 // interleaved by 2^16); n = 32 with four QPUs, partitioned: 592 -> 565 ms.
 constexpr int kIlvBit = 16;
 
+// Whether the specialised kernels of the precision run this plan's passes.
+bool fast_plan(const qq_problem *pb, const Plan &plan, int flags)
+{
+    if (plan.sets.size() < 2 || pb->n > kFastMaxN) return false;
+    return !((flags & QQ_C128) && (flags & QQ_PARTITIONED));
+}
+
 struct Layout {
     size_t psi = 0, lam = 0, partial = 0, params = 0, out = 0, total = 0;
     size_t stride = 0;  // amplitudes from one state's region to the next
@@ -686,7 +693,7 @@ const qq_problem::CostTab *find_table(const std::vector<qq_problem::CostTab> &ta
 
 // Run every pass of a plan and the final reduction.  `ws` is device memory laid out by `L`.
 qq_status run_plan(qq_problem *pb, const Plan &plan, const Layout &L, int p, int B, int flags, char *ws,
-                   const double *d_params, hipStream_t stream, bool capturing = false)
+                   const double *d_params, hipStream_t stream, const EvalOut &out, bool capturing = false)
 {
     const bool prof = g_prof && !capturing;  // no event records inside a captured graph
     const bool c128 = flags & QQ_C128;
@@ -694,8 +701,11 @@ qq_status run_plan(qq_problem *pb, const Plan &plan, const Layout &L, int p, int
     const size_t es = c128 ? 16 : 8;
     (void)es;
     if (plan.nslots > kMaxSlots) return fail(QQ_E_UNSUPPORTED, "plan needs %d accumulator slots (max %d)", plan.nslots, kMaxSlots);
-    // Specialised complex64 kernels serve multi-pass, non-partitioned plans.
-    const bool use_fast = !c128 && plan.sets.size() > 1 && pb->n <= kFastMaxN;
+    // The specialised kernels serve every multi-pass plan but the partitioned complex128 ones.
+    const bool use_fast = fast_plan(pb, plan, flags);
+    // a single pass (n <= 12, one workgroup per set) writes the results itself
+    const bool single = plan.sets.size() == 1;
+    const double escale = pb->n < kTileBits ? std::ldexp(1.0, pb->n - kTileBits) : 1.0;
     int slot_base = 0;
     for (const auto &pp : plan.passes) {
         if ((int)pp.ops.size() > kMaxOps) return fail(QQ_E_UNSUPPORTED, "pass has %zu ops (max %d)", pp.ops.size(), kMaxOps);
@@ -729,6 +739,11 @@ qq_status run_plan(qq_problem *pb, const Plan &plan, const Layout &L, int p, int
         a.cross_diag = pb->d_cross;
         a.part = pb->d_part;
         for (size_t i = 0; i < pp.ops.size(); ++i) a.ops[i] = pp.ops[i];
+        if (single) {
+            a.out = out;
+            a.escale = escale;
+            for (size_t i = 0; i < pp.slot_out.size(); ++i) a.slot_out[i] = (uint8_t)pp.slot_out[i];
+        }
         ProfRec rec{};
         if (prof) {
             QQ_HIP(hipEventCreate(&rec.start));
@@ -780,7 +795,19 @@ qq_status run_plan(qq_problem *pb, const Plan &plan, const Layout &L, int p, int
                 fp.xtab = xt->rows;
                 fp.xthr = xt->thr;
             }
-            QQ_HIP(launch_fast_pass(pp.fkind, sd.high != 0, pb->diag_type, fp, stream));
+            if (c128) QQ_HIP(launch_fast_pass128(pp.fkind, sd.high != 0, fp, stream));
+            else QQ_HIP(launch_fast_pass(pp.fkind, sd.high != 0, pb->diag_type, fp, stream));
+        } else if (single && c128 && !(flags & QQ_PARTITIONED)) {
+            SingleArgs sa;
+            sa.n = pb->n;
+            sa.p = p;
+            sa.amp0 = a.amp0;
+            sa.escale = escale;
+            sa.params = d_params;
+            sa.diag = pb->d_diag;
+            sa.psi = (pp.flags & PF_STORE_PSI) ? a.psi : nullptr;
+            sa.out = out;
+            QQ_HIP(launch_single128(sa, B, pp.nstates > 1, pb->diag_type, stream));
         } else {
             QQ_HIP(launch_pass(a, c128, pp.nstates, pb->diag_type, stream));
         }
@@ -801,17 +828,18 @@ qq_status run_plan(qq_problem *pb, const Plan &plan, const Layout &L, int p, int
         }
         slot_base += a.nslots;
     }
+    if (single) return QQ_OK;
     FinalizeArgs fa;
     std::memset(&fa, 0, sizeof fa);
     fa.B = B;
     fa.G = L.G;
     fa.p = p;
     fa.nslots = plan.nslots;
-    fa.escale = pb->n < kTileBits ? std::ldexp(1.0, pb->n - kTileBits) : 1.0;
-    // the specialised kernels accumulate with C - alpha (every pass of a multi-pass complex64 plan)
-    fa.shift = (use_fast && !plan.passes.empty() && plan.passes[0].fkind >= 0) ? pb->alpha : 0.0;
+    fa.escale = escale;
+    // the complex64 specialised kernels accumulate with C - alpha (every pass of a multi-pass plan)
+    fa.shift = (use_fast && !c128 && !plan.passes.empty() && plan.passes[0].fkind >= 0) ? pb->alpha : 0.0;
     fa.partial = reinterpret_cast<const double *>(ws + L.partial);
-    fa.out = reinterpret_cast<double *>(ws + L.out);
+    fa.out = out;
     int s = 0;
     for (const auto &pp : plan.passes)
         for (int o : pp.slot_out) fa.slot_out[s++] = (uint16_t)o;
@@ -847,9 +875,16 @@ qq_status validate_eval(const qq_problem *pb, int p, int batch, int flags)
     return QQ_OK;
 }
 
-// Evaluate a plan for `batch` parameter sets into ws; leaves results at ws + L.out on the device.
+// The workspace's result block: [B][1 + 2p], energy then gradient.
+EvalOut ws_out(char *ws, const Layout &L, int p, int flags)
+{
+    double *o = reinterpret_cast<double *>(ws + L.out);
+    return {o, (flags & QQ_GRAD) ? o + 1 : nullptr, 1 + 2 * p, 1 + 2 * p};
+}
+
+// Evaluate a plan for `batch` parameter sets, results to `out` (device memory).
 qq_status eval_core(qq_problem *pb, int p, int batch, const double *params, int flags, const Plan &plan,
-                    const Layout &L, char *ws, hipStream_t stream)
+                    const Layout &L, char *ws, hipStream_t stream, const EvalOut &out, bool capturing = false)
 {
     const double *d_params = params;
     if (!(flags & QQ_PARAMS_ON_DEVICE)) {
@@ -857,7 +892,7 @@ qq_status eval_core(qq_problem *pb, int p, int batch, const double *params, int 
         QQ_HIP(hipMemcpyAsync(ws + L.params, params, (size_t)batch * 2 * p * sizeof(double), hipMemcpyHostToDevice,
                               stream));
     }
-    return run_plan(pb, plan, L, p, batch, flags, ws, d_params, stream);
+    return run_plan(pb, plan, L, p, batch, flags, ws, d_params, stream, out, capturing);
 }
 
 // ---- many problems in one persistent launch -----------------------------------------------
@@ -867,7 +902,6 @@ struct ManyGroup {
     std::vector<int> members;  // problem indices, in queue priority order
     std::vector<ManyInst> inst;
     std::vector<ManyPass> pass;
-    std::vector<PassArgs> gpass;  // complex128: the general pass of each entry of `pass`
     std::vector<ManySeg> seg;
     std::vector<uint16_t> slot_out;
     uint32_t total = 0;
@@ -877,7 +911,7 @@ struct ManyGroup {
     double bytes = 0;  // algorithmic HBM bytes of the launch
     // workspace offsets
     size_t ctl = 0, desc = 0, partial = 0, states = 0;
-    size_t inst_off = 0, pass_off = 0, gpass_off = 0, seg_off = 0, slot_off = 0, desc_bytes = 0;
+    size_t inst_off = 0, pass_off = 0, seg_off = 0, slot_off = 0, desc_bytes = 0;
 };
 
 struct ManyLayout {
@@ -922,7 +956,8 @@ namespace {
 // One optimisation step on `stream`: the evaluation's pass and finalize kernels, then Adam.
 qq_status enqueue_step(qq_graph *g, hipStream_t stream, bool capturing)
 {
-    if (qq_status st = run_plan(g->pb, g->plan, g->L, g->p, g->B, g->flags, g->ws, g->x, stream, capturing);
+    if (qq_status st = run_plan(g->pb, g->plan, g->L, g->p, g->B, g->flags, g->ws, g->x, stream,
+                                ws_out(g->ws, g->L, g->p, g->flags), capturing);
         st != QQ_OK)
         return st;
     AdamArgs a;
@@ -1155,57 +1190,7 @@ qq_status plan_many(int count, qq_problem *const *pbs, const int *p, const int *
             I.pass_off = (int)G.pass.size();
             I.slot_off = (int)G.slot_out.size();
             I.partial_off = G.partial_doubles;
-            if (c128) {
-                // complex128: the general pass bodies, chunks of tiles for every problem (one pass of
-                // one tile for n <= 12); the passes accumulate with C itself (shift 0)
-                I.tpc = many_tiles_per_chunk(I.tiles, opt, c128);
-                I.nchunks = (int)((I.tiles + (uint64_t)I.tpc - 1) / (uint64_t)I.tpc);
-                I.npasses = (int)plan.passes.size();
-                int slot_base = 0;
-                for (const PassPlan &pp : plan.passes) {
-                    const SetDesc &sd = plan.sets[pp.set];
-                    if ((int)pp.ops.size() > kMaxOps)
-                        return fail(QQ_E_UNSUPPORTED, "pass has %zu ops (max %d)", pp.ops.size(), kMaxOps);
-                    ManyPass P;
-                    std::memset(&P, 0, sizeof P);
-                    P.kind = -1;
-                    P.geom = pp.nstates;
-                    P.slot_base = slot_base;
-                    P.nslots = (int)pp.slot_out.size();
-                    PassArgs a;
-                    std::memset(&a, 0, sizeof a);
-                    a.n = pb->n;
-                    a.p = I.p;
-                    a.B = I.B;
-                    a.G = 1;
-                    a.tiles = I.tiles;
-                    a.dim_mask = I.dim_mask;
-                    a.pos4 = sd.pos4;
-                    a.pos8 = sd.pos8;
-                    a.high = sd.high;
-                    a.w1 = sd.pos4 - 4;
-                    a.w2 = sd.pos8 - sd.pos4 - 4;
-                    a.flags = pp.flags;
-                    a.nops = (int)pp.ops.size();
-                    a.nslots = P.nslots;
-                    a.amp0 = I.amp0;
-                    a.state_stride = pb->dim;  // params, diag, psi, lam: device addresses, set at launch
-                    for (size_t o = 0; o < pp.ops.size(); ++o) a.ops[o] = pp.ops[o];
-                    slot_base += P.nslots;
-                    for (int o : pp.slot_out) G.slot_out.push_back((uint16_t)o);
-                    G.pass.push_back(P);
-                    G.gpass.push_back(a);
-                    G.bytes += pass_bytes(pb, pp, I.B, true, false);
-                }
-                I.nslots = slot_base;
-                const size_t sb = (size_t)pb->dim * 16 * I.B;
-                I.psi = reinterpret_cast<void *>(state_off);  // relative; fixed up at launch
-                state_off += align_up(sb);
-                if (grad) {
-                    I.lam = reinterpret_cast<void *>(state_off);
-                    state_off += align_up(sb);
-                }
-            } else if (plan.sets.size() == 1) {
+            if (plan.sets.size() == 1) {
                 // the whole evaluation in one item per parameter set; slot o is output o
                 ManyPass P;
                 std::memset(&P, 0, sizeof P);
@@ -1221,7 +1206,7 @@ qq_status plan_many(int count, qq_problem *const *pbs, const int *p, const int *
                 for (int o = 0; o < I.nslots; ++o) G.slot_out.push_back((uint16_t)o);
                 G.bytes += (double)pb->dim * diag_bytes_of(pb->diag_type);
             } else {
-                I.shift = pb->alpha;  // the pass bodies accumulate with C - alpha
+                I.shift = c128 ? 0.0 : pb->alpha;  // the complex64 pass bodies accumulate with C - alpha
                 I.tpc = many_tiles_per_chunk(I.tiles, opt, c128);
                 I.nchunks = (int)((I.tiles + (uint64_t)I.tpc - 1) / (uint64_t)I.tpc);
                 I.npasses = (int)plan.passes.size();
@@ -1249,10 +1234,10 @@ qq_status plan_many(int count, qq_problem *const *pbs, const int *p, const int *
                     slot_base += P.nslots;
                     for (int o : pp.slot_out) G.slot_out.push_back((uint16_t)o);
                     G.pass.push_back(P);
-                    G.bytes += pass_bytes(pb, pp, I.B, false, true);
+                    G.bytes += pass_bytes(pb, pp, I.B, c128, true);
                 }
                 I.nslots = slot_base;
-                const size_t sb = (size_t)pb->dim * sizeof(float2) * I.B;
+                const size_t sb = (size_t)pb->dim * (c128 ? 16 : 8) * I.B;
                 I.psi = reinterpret_cast<void *>(state_off);  // relative; fixed up below
                 state_off += align_up(sb);
                 if (grad) {
@@ -1298,8 +1283,7 @@ qq_status plan_many(int count, qq_problem *const *pbs, const int *p, const int *
         off += align_up((size_t)(2 + G.nstates) * sizeof(uint32_t));
         G.inst_off = 0;
         G.pass_off = align_up(G.inst.size() * sizeof(ManyInst), 16);
-        G.gpass_off = G.pass_off + align_up(G.pass.size() * sizeof(ManyPass), 16);
-        G.seg_off = G.gpass_off + align_up(G.gpass.size() * sizeof(PassArgs), 16);
+        G.seg_off = G.pass_off + align_up(G.pass.size() * sizeof(ManyPass), 16);
         G.slot_off = G.seg_off + align_up(G.seg.size() * sizeof(ManySeg), 16);
         G.desc_bytes = G.slot_off + G.slot_out.size() * sizeof(uint16_t);
         G.desc = off;
@@ -1971,20 +1955,19 @@ static qq_status evaluate_impl(qq_problem *pb, int p, int batch, const double *p
         return fail(QQ_E_WORKSPACE, "workspace of %zu bytes, need %zu", ws_bytes, L.total);
     }
     QQ_HIP(poison(ws, L.total, stream));
-    if (qq_status st = eval_core(pb, p, batch, params, flags, plan, L, ws, stream); st != QQ_OK) return st;
-    const double *d_out = reinterpret_cast<const double *>(ws + L.out);
-    const size_t nout = 1 + 2 * (size_t)p;
     const bool grad = flags & QQ_GRAD;
     if (flags & QQ_OUT_ON_DEVICE) {
-        QQ_HIP(hipMemcpy2DAsync(energy_out, sizeof(double), d_out, nout * sizeof(double), sizeof(double), batch,
-                                hipMemcpyDeviceToDevice, stream));
-        if (grad)
-            QQ_HIP(hipMemcpy2DAsync(grad_out, 2 * p * sizeof(double), d_out + 1, nout * sizeof(double),
-                                    2 * p * sizeof(double), batch, hipMemcpyDeviceToDevice, stream));
+        const EvalOut out = {energy_out, grad ? grad_out : nullptr, 1, 2 * p};
+        if (qq_status st = eval_core(pb, p, batch, params, flags, plan, L, ws, stream, out); st != QQ_OK) return st;
         if (own.p) QQ_HIP(hipStreamSynchronize(stream));
         own.done();
         return QQ_OK;
     }
+    if (qq_status st = eval_core(pb, p, batch, params, flags, plan, L, ws, stream, ws_out(ws, L, p, flags));
+        st != QQ_OK)
+        return st;
+    const double *d_out = reinterpret_cast<const double *>(ws + L.out);
+    const size_t nout = 1 + 2 * (size_t)p;
     std::vector<double> h((size_t)batch * nout);
     QQ_HIP(hipMemcpyAsync(h.data(), d_out, h.size() * sizeof(double), hipMemcpyDeviceToHost, stream));
     QQ_HIP(hipStreamSynchronize(stream));
@@ -2018,23 +2001,19 @@ static qq_status evaluate_static_impl(qq_problem *pb, int p, int batch, const do
     QQ_HIP(static_scratch(pb->device, &sp));
     char *ws = static_cast<char *>(sp);
     QQ_HIP(poison(ws, L.total, stream));
-    const double *d_params = params;
-    if (!(flags & QQ_PARAMS_ON_DEVICE)) {
-        d_params = reinterpret_cast<const double *>(ws + L.params);
-        QQ_HIP(hipMemcpyAsync(ws + L.params, params, (size_t)batch * 2 * p * sizeof(double), hipMemcpyHostToDevice,
-                              stream));
-    }
+    const bool grad = flags & QQ_GRAD, dev_out = flags & QQ_OUT_ON_DEVICE;
+    const EvalOut out = dev_out ? EvalOut{energy_out, grad ? grad_out : nullptr, 1, 2 * p} : ws_out(ws, L, p, flags);
     // no profiling events here (capturing = true): they are not part of the computation
-    if (qq_status st = run_plan(pb, plan, L, p, batch, flags, ws, d_params, stream, true); st != QQ_OK) return st;
-    const double *d_out = reinterpret_cast<const double *>(ws + L.out);
-    const size_t nout = 1 + 2 * (size_t)p;
-    const bool grad = flags & QQ_GRAD;
-    const hipMemcpyKind kind = (flags & QQ_OUT_ON_DEVICE) ? hipMemcpyDeviceToDevice : hipMemcpyDeviceToHost;
-    QQ_HIP(hipMemcpy2DAsync(energy_out, sizeof(double), d_out, nout * sizeof(double), sizeof(double), batch, kind,
-                            stream));
-    if (grad)
-        QQ_HIP(hipMemcpy2DAsync(grad_out, 2 * p * sizeof(double), d_out + 1, nout * sizeof(double),
-                                2 * p * sizeof(double), batch, kind, stream));
+    if (qq_status st = eval_core(pb, p, batch, params, flags, plan, L, ws, stream, out, true); st != QQ_OK) return st;
+    if (!dev_out) {
+        const double *d_out = reinterpret_cast<const double *>(ws + L.out);
+        const size_t nout = 1 + 2 * (size_t)p;
+        QQ_HIP(hipMemcpy2DAsync(energy_out, sizeof(double), d_out, nout * sizeof(double), sizeof(double), batch,
+                                hipMemcpyDeviceToHost, stream));
+        if (grad)
+            QQ_HIP(hipMemcpy2DAsync(grad_out, 2 * p * sizeof(double), d_out + 1, nout * sizeof(double),
+                                    2 * p * sizeof(double), batch, hipMemcpyDeviceToHost, stream));
+    }
     if (!(flags & QQ_OUT_ON_DEVICE)) QQ_HIP(hipStreamSynchronize(stream));
     return QQ_OK;
 }
@@ -2054,7 +2033,8 @@ static qq_status state_into(qq_problem *pb, int p, const double *params, int fla
     if (qq_status st = check_device_fits(pb->device, L.total, "the state"); st != QQ_OK) return st;
     if (own.get(pb->device, L.total) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) failed", L.total);
     QQ_HIP(poison(own.p, L.total, stream));
-    return eval_core(pb, p, 1, params, f, plan, L, static_cast<char *>(own.p), stream);
+    char *ws = static_cast<char *>(own.p);
+    return eval_core(pb, p, 1, params, f, plan, L, ws, stream, ws_out(ws, L, p, f));
 }
 
 qq_status qq_state(qq_problem *pb, int p, const double *params, int flags, void *psi_out, void *stream_)
@@ -2434,15 +2414,6 @@ static qq_status evaluate_many_impl(int count, qq_problem *const *problems, cons
                 I.psi = ws + G.states + reinterpret_cast<size_t>(I.psi);
                 I.lam = grad ? ws + G.states + reinterpret_cast<size_t>(I.lam) : nullptr;
             }
-            if (!G.gpass.empty()) {
-                for (int j = I.pass_off; j < I.pass_off + I.npasses; ++j) {
-                    PassArgs &a = G.gpass[j];
-                    a.params = I.params;
-                    a.diag = I.diag;
-                    a.psi = I.psi;
-                    a.lam = I.lam;
-                }
-            }
             if (flags & QQ_OUT_ON_DEVICE) {
                 I.energy_out = energy_out[i];
                 I.grad_out = grad ? grad_out[i] : nullptr;
@@ -2457,8 +2428,6 @@ static qq_status evaluate_many_impl(int count, qq_problem *const *problems, cons
         blob.assign(G.desc_bytes, 0);
         std::memcpy(blob.data() + G.inst_off, G.inst.data(), G.inst.size() * sizeof(ManyInst));
         std::memcpy(blob.data() + G.pass_off, G.pass.data(), G.pass.size() * sizeof(ManyPass));
-        if (!G.gpass.empty())
-            std::memcpy(blob.data() + G.gpass_off, G.gpass.data(), G.gpass.size() * sizeof(PassArgs));
         std::memcpy(blob.data() + G.seg_off, G.seg.data(), G.seg.size() * sizeof(ManySeg));
         std::memcpy(blob.data() + G.slot_off, G.slot_out.data(), G.slot_out.size() * sizeof(uint16_t));
         QQ_HIP(hipMemcpyAsync(ws + G.desc, blob.data(), G.desc_bytes, hipMemcpyHostToDevice, stream));
@@ -2468,7 +2437,6 @@ static qq_status evaluate_many_impl(int count, qq_problem *const *problems, cons
         ManyArgs a;
         a.inst = reinterpret_cast<const ManyInst *>(ws + G.desc + G.inst_off);
         a.pass = reinterpret_cast<const ManyPass *>(ws + G.desc + G.pass_off);
-        a.gpass = G.gpass.empty() ? nullptr : reinterpret_cast<const PassArgs *>(ws + G.desc + G.gpass_off);
         a.seg = reinterpret_cast<const ManySeg *>(ws + G.desc + G.seg_off);
         a.slot_out = reinterpret_cast<const uint16_t *>(ws + G.desc + G.slot_off);
         a.nseg = (int)G.seg.size();
@@ -2849,8 +2817,9 @@ qq_status qq_autotune(qq_problem *pb, int p, int batch, int flags, const char *c
         L.blocked = order;
         double ms = 0;
         auto run = [&]() {
-            return run_plan(pb, plan, L, p, batch, eflags, static_cast<char *>(ws.p), static_cast<const double *>(dx.p),
-                            stream, true);
+            char *w = static_cast<char *>(ws.p);
+            return run_plan(pb, plan, L, p, batch, eflags, w, static_cast<const double *>(dx.p), stream,
+                            ws_out(w, L, p, eflags), true);
         };
         if (qq_status st = time_median(stream, run, ms); st != QQ_OK) return st;
         ++tried;
@@ -2866,8 +2835,7 @@ qq_status qq_autotune(qq_problem *pb, int p, int batch, int flags, const char *c
     for (int pr = 0; pr < npair; ++pr)
         for (int G : Gs)
             if (qq_status st = time_one(pr, G, 0, so0); st != QQ_OK) return st;
-    const bool multi_pass = make_sets(pb->n, 0).size() > 1 && !(flags & QQ_C128) && pb->n <= kFastMaxN;
-    if (multi_pass) {  // the tile order only applies to the specialised multi-pass kernels
+    if (fast_plan(pb, plan0, flags)) {  // the tile order only applies to the specialised multi-pass kernels
         const int pr = bestP;
         for (int G : g_candidates(bestG))
             if (qq_status st = time_one(pr, G, 1, so0); st != QQ_OK) return st;

@@ -73,6 +73,15 @@ struct PartDesc {
     uint64_t vmask[QQ_MAX_QPUS];      // bit i set when variable i + 1 sits on QPU m
 };
 
+// Where an evaluation's results go: energy of set b at energy[b * estride], its interleaved gradient
+// at grad[b * gstride ..] (NULL: none).  The workspace's [B][1 + 2p] block, or the caller's device
+// buffers directly.
+struct EvalOut {
+    double *energy;
+    double *grad;
+    int estride, gstride;
+};
+
 struct PassArgs {
     int n;
     int p;
@@ -98,6 +107,10 @@ struct PassArgs {
     const void *part_tables;  // packed local tables (diag element type)
     const void *cross_diag;   // 2^n cross diagonal (diag element type)
     const PartDesc *part;     // device
+    // a plan's only pass writes the results itself: slot s is output slot_out[s]
+    EvalOut out;
+    double escale;
+    uint8_t slot_out[kMaxImmSlots];
     Op ops[kMaxOps];
 };
 
@@ -109,7 +122,7 @@ struct FinalizeArgs {
     double escale;        // 2^(n-12) for replicated small states, else 1
     double shift;         // added to the energy: the passes accumulated sum |psi|^2 (C - shift)
     const double *partial;
-    double *out;          // [B][1 + 2p] : energy, then interleaved gradient
+    EvalOut out;
     uint16_t slot_out[kMaxSlots];  // output index of each global slot
 };
 
@@ -167,6 +180,21 @@ struct FastPassParams {
     int ilv;  // 0, or K: psi and lambda in alternating blocks of 2^K amplitudes (see Layout::ilv)
 };
 hipError_t launch_fast_pass(int kind, bool high, int diag_type, const FastPassParams &pp, hipStream_t s);
+// The same passes on complex128 states (qq_fast128.hip): monolithic phases, costs from the tables,
+// accumulations with C itself (no shift).
+hipError_t launch_fast_pass128(int kind, bool high, const FastPassParams &pp, hipStream_t s);
+
+// Whole complex128 evaluations of a problem with n <= 12, one workgroup per parameter set; results
+// (and with psi the final states) written by the kernel itself.
+struct SingleArgs {
+    int n, p;
+    double amp0, escale;  // escale: 2^(n-12) (replicated tile)
+    const double *params;  // device [B][2p]
+    const void *diag;
+    void *psi;  // [B][2^n] complex128 or NULL
+    EvalOut out;
+};
+hipError_t launch_single128(const SingleArgs &a, int B, bool grad, int diag_type, hipStream_t s);
 
 // Per-tile cost table of one tile geometry and layout (qq_kernels.hip).  A tile's 4096 states are
 // z = T + E + R: T its base bits, E the thread's bits (qubits 0..3 and the two lane qubits at lane_q:
@@ -204,14 +232,13 @@ struct ManyInst {
     const double *params;   // device [B][2p]
     const void *diag;
     const double *regq;     // device [n - 3][16]: register-run coupling sums (see qq_problem::regq)
-    void *psi, *lam;        // device [B][2^n] complex64 (multi-pass problems), complex128 (every problem)
+    void *psi, *lam;        // device [B][2^n] states of multi-pass problems (complex64 or complex128)
     double *energy_out;     // device [B], or NULL: results go to out_ws
     double *grad_out;       // device [B][2p] (with energy_out)
     double *out_ws;         // device [B][1 + 2p]
 };
 struct ManyPass {
     int kind, k, geom;      // geom 0: qubits 0..11; 1: high set, all 8 bits active; 2: high set, partial
-                            // (complex128 launch: kind -1, geom = states the general pass keeps, 1 or 2)
     int pos4, pos8, w1, w2, active, nact, store_psi;
     int slot_base, nslots;  // first accumulator slot of the pass inside its problem
     const double *ctab;     // the cost table of the pass's layout and its per-thread constants
@@ -224,7 +251,6 @@ struct ManySeg {
 struct ManyArgs {
     const ManyInst *inst;
     const ManyPass *pass;
-    const PassArgs *gpass;  // complex128 launch: the general pass of each ManyPass (same index), else NULL
     const ManySeg *seg;
     const uint16_t *slot_out;
     int nseg;

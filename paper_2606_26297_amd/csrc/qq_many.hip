@@ -6,9 +6,8 @@
 // on a state once every chunk of pass j on that state has completed.  A problem
 // with n <= 12 is a single item: one workgroup runs the whole evaluation (all p
 // layers, the energy and the adjoint sweep) on one register-resident tile.
-// The complex128 launch (many128_kernel) runs the general pass bodies on
-// complex128 states instead, one chunk of tiles per item for every problem
-// (a problem with n <= 12 has one pass of one tile).
+// The complex128 launch (many128_kernel) does the same with the complex128
+// bodies.
 //
 // Ordering and progress.  Tickets are handed out in increasing order from one
 // atomic counter, and items are numbered so that every pass of a state comes
@@ -30,8 +29,7 @@
 // its own; the workgroup that completes the last item of a state sums the
 // partials in a fixed order (slots ascending, chunks ascending), so results are
 // reproducible run to run.
-#include "qq_generic.h"
-#include "qq_passes.h"
+#include "qq_passes128.h"
 
 namespace qq {
 namespace {
@@ -404,25 +402,94 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3
     });
 }
 
-// Complex128 states: the general pass body of item (problem, parameter set b, pass, chunk) over the
-// chunk's consecutive tiles, its slot totals into the item's partial sums.
-template <typename DT>
-__global__ void __launch_bounds__(kThreads) many128_kernel(const ManyArgs A)
+// ---- complex128 states -------------------------------------------------------------------------
+template <int KIND>
+__device__ __forceinline__ void run_geom128(int geom, const p128::Args &a, double2 *lds, double (&acc)[3], int t, int b,
+                                            int g)
 {
-    __shared__ gen::GenShared<double> sh;
+    const p128::Coef f = p128::coef<KIND>(a.params + (size_t)b * 2 * a.p, a.k);
+    // one-state kinds transpose in two rounds of 8-byte words (registers bound this kernel, not LDS)
+    using W = typename std::conditional<kind_states<KIND>() == 2, double2, double>::type;
+    W *l = reinterpret_cast<W *>(lds);
+    if (geom == 0) {
+        p128::pass_body<KIND, false, true>(a, l, acc, t, b, g, f);
+    } else if constexpr (KIND != FK_FIRST) {  // the persistent plans take the qubit-0..11 set first
+        if (geom == 1) p128::pass_body<KIND, true, true>(a, l, acc, t, b, g, f);
+        else p128::pass_body<KIND, true, false>(a, l, acc, t, b, g, f);
+    }
+}
+
+__device__ __forceinline__ void run_chunk128(const ManyInst &I, const ManyPass &P, double *partial, double2 *lds,
+                                             double *s_red, int t, int b, int chunk)
+{
+    p128::Args a;
+    const uint64_t t0 = (uint64_t)chunk * (uint64_t)I.tpc;
+    a.B = I.B;
+    a.G = 1;  // consecutive tiles
+    a.p = I.p;
+    a.k = P.k;
+    a.tiles = min(I.tiles, t0 + (uint64_t)I.tpc);
+    a.pos4 = P.pos4;
+    a.pos8 = P.pos8;
+    a.w1 = P.w1;
+    a.w2 = P.w2;
+    a.active = P.active;
+    a.store_psi = P.store_psi;
+    a.slot_base = 0;
+    a.slot_stride = 0;
+    a.amp0 = I.amp0;
+    a.params = I.params;
+    a.psi = static_cast<double2 *>(I.psi);
+    a.lam = static_cast<double2 *>(I.lam);
+    a.state_stride = I.dim_mask + 1;
+    a.partial = nullptr;
+    a.blocked = 0;
+    a.cq = I.regq + 16 * (P.kind == FK_FIRST ? P.pos8 : P.pos4);
+    a.ctab = P.ctab;
+    a.cthr = P.cthr;
+    double acc[3] = {0.0, 0.0, 0.0};
+    const int g = (int)t0;
+    switch (P.kind) {
+    case FK_FIRST: run_geom128<FK_FIRST>(P.geom, a, lds, acc, t, b, g); break;
+    case FK_MID: run_geom128<FK_MID>(P.geom, a, lds, acc, t, b, g); break;
+    case FK_TURN: run_geom128<FK_TURN>(P.geom, a, lds, acc, t, b, g); break;
+    case FK_LAST: run_geom128<FK_LAST>(P.geom, a, lds, acc, t, b, g); break;
+    case FK_LASTG: run_geom128<FK_LASTG>(P.geom, a, lds, acc, t, b, g); break;
+    case FK_BMID: run_geom128<FK_BMID>(P.geom, a, lds, acc, t, b, g); break;
+    case FK_BTURN: run_geom128<FK_BTURN>(P.geom, a, lds, acc, t, b, g); break;
+    default: run_geom128<FK_BLAST>(P.geom, a, lds, acc, t, b, g); break;
+    }
+#pragma unroll
+    for (int s = 0; s < 3; ++s) {
+        if (s >= P.nslots) break;
+        const double v = wg_sum(acc[s], s_red, t);
+        if (t == 0) partial[I.partial_off + ((size_t)(P.slot_base + s) * I.B + b) * I.nchunks + chunk] = v;
+    }
+}
+
+// The specialised complex128 bodies behind the same queue, two workgroups per compute unit (the
+// operation-list bodies took 488 registers, one workgroup per unit).
+template <typename DT>
+__global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) many128_kernel(const ManyArgs A)
+{
+    __shared__ double2 lds[kLdsSlots];
+    __shared__ double s_red[kThreads / 64];
     __shared__ uint32_t s_msg[2];
+    __shared__ double2 s_cs[QQ_MAX_P];
     const int t = threadIdx.x;
     drain_queue(A, s_msg, t, [&](const ManyInst &I, int pass, int b, int chunk) __attribute__((always_inline)) {
         const ManyPass &P = A.pass[I.pass_off + pass];
-        const PassArgs &a = A.gpass[I.pass_off + pass];
-        gen::gen_setup<double>(sh, I.params + (size_t)b * 2 * I.p, I.p, t);
-        double acc[kMaxLocalSlots] = {0.0, 0.0, 0.0, 0.0};
-        const uint64_t t0 = (uint64_t)chunk * (uint64_t)I.tpc, t1 = min(I.tiles, t0 + (uint64_t)I.tpc);
-        if (P.geom > 1) gen::gen_tiles<double, 2, DT>(a, sh, t, b, t0, t1, 1, acc);
-        else gen::gen_tiles<double, 1, DT>(a, sh, t, b, t0, t1, 1, acc);
-        gen::gen_slot_totals<double>(P.nslots, acc, sh, t, [&](int s, double sum) __attribute__((always_inline)) {
-            A.partial[I.partial_off + ((size_t)(P.slot_base + s) * I.B + b) * I.nchunks + chunk] = sum;
-        });
+        int ti = t;
+        asm volatile("" : "+v"(ti));  // each body forms its indexes itself
+        if (P.kind == FK_SINGLE) {
+            const p128::Single e = {I.n, I.p, I.amp0, I.params + (size_t)b * 2 * I.p, I.diag};
+            double *out = A.partial + I.partial_off + b;  // slot o at out[o * B]
+            auto put = [&](int o, double v) __attribute__((always_inline)) { out[(size_t)o * I.B] = v; };
+            if (A.grad) p128::single_eval<2, DT>(e, lds, s_red, s_cs, ti, nullptr, put);
+            else p128::single_eval<1, DT>(e, lds, s_red, s_cs, ti, nullptr, put);
+        } else {
+            run_chunk128(I, P, A.partial, lds, s_red, ti, b, chunk);
+        }
     });
 }
 

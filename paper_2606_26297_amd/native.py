@@ -777,9 +777,13 @@ def kernel_name(rec) -> str:
     dt = DIAG_TYPE_NAMES[rec["diag_bytes"]]
     if rec["pass_kind"] >= 0:
         tf = lambda x: "true" if x else "false"  # noqa: E731
+        if rec["c128"]:
+            return f"fast_pass128<{rec['pass_kind']}, {tf(rec['high'])}, {tf(rec['full'])}>"
         name = "fast_pass_part" if rec.get("part") else "fast_pass"
         if rec["high"] and not rec["full"] and rec["n"] >= 32:  # 64-bit lane offsets
             return f"{name}_wide<{rec['pass_kind']}, {dt}>"
         return f"{name}<{rec['pass_kind']}, {tf(rec['high'])}, {tf(rec['full'])}, {dt}>"
+    if rec["c128"] and not rec.get("part"):  # n <= 12
+        return f"single128<{2 if rec['kind'] == 2 else 1}, {dt}>"
     real = "double" if rec["c128"] else "float"
     return f"pass_kernel<{real}, {2 if rec['kind'] == 2 else 1}, {dt}>"
