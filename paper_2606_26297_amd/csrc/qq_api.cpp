@@ -1116,18 +1116,20 @@ uint64_t fnv1a(uint64_t h, int64_t v)
     return h;
 }
 
-int many_tiles_per_chunk(uint64_t tiles, const qq_many_options *opt, bool c128)
+// Tiles per item when the caller leaves them open.  An item of c tiles costs the launch a share of one
+// ticket, one wait and one completion (about 0.04 us of the whole chip per item in complex64, 0.07 in
+// complex128, from one-tile items: 512 problems 35.7 ms against 18.9, 128 problems 10.7 against 4.8),
+// so `items` one-tile items cost items * o / c; the longest chain of dependent passes runs its tiles one
+// after the other in at least L * c * u (u = 4 and 6.5 us per tile beside others).  The sum is least at
+// c = sqrt(items * o / (L * u)).  Measured (complex64, ms at 1 / 2 / 4 / 8 / 12 / 24 tiles, the rule's
+// choice): 512 problems of n <= 22 35.7 / 22.3 / 20.3 / 19.3 / 19.1 / 18.9 (19); 128 10.7 / 6.5 / 5.3 / 4.8 /
+// 5.0 / 6.5 (10); 96 of n <= 21 2.5 / 1.7 / 1.5 / 1.7 / 2.1 / 3.0 (6); 20 1.23 / 0.95 / 0.74 / 0.86 / 0.98 / 1.6
+// (3); 128 of n <= 14 0.14 / 0.18 / 0.28 (1).
+int many_tiles_per_chunk(double items, int longest, const qq_many_options *opt, bool c128)
 {
-    // 24 tiles (768 KiB of one complex64 state) per item: each item ends with an XCD-wide
-    // cache write-back and two device-scope atomics, which such an item amortises, while a
-    // 2^22-amplitude pass still splits into 43 items (measured on MI355X with the 512-problem
-    // uneven batch: 1 tile 107 ms, 8 tiles 30 ms in an earlier version; now 16 tiles 22.0 ms,
-    // 24 20.9, 32 21.1, 48 22.0, 64 23.6).
-    // Complex128 (one resident workgroup per compute unit): 8 tiles, so that the longest pass
-    // chains split finely (the batch's 88 flagged sets: 2 tiles 13.5 ms, 4 11.4, 8 10.6, 16 11.8,
-    // 64 25.5)
-    const uint64_t want = (opt && opt->tiles_per_chunk > 0) ? (uint64_t)opt->tiles_per_chunk : (c128 ? 8 : 24);
-    return (int)std::min<uint64_t>(want, tiles);
+    if (opt && opt->tiles_per_chunk > 0) return opt->tiles_per_chunk;
+    const double o = c128 ? 0.07 : 0.04, u = c128 ? 6.5 : 4.0;
+    return (int)std::min(64.0, std::max(1.0, std::nearbyint(std::sqrt(items * o / (std::max(1, longest) * u)))));
 }
 
 qq_status plan_many(int count, qq_problem *const *pbs, const int *p, const int *batch, int flags,
@@ -1161,6 +1163,14 @@ qq_status plan_many(int count, qq_problem *const *pbs, const int *p, const int *
         M.out_off[i] = ooff;
         ooff += (size_t)batch[i] * (1 + 2 * p[i]);
     }
+    double one_tile_items = 0.0;
+    int longest = 1;
+    for (int i = 0; i < count; ++i) {
+        if (plans[i].sets.size() == 1) continue;
+        one_tile_items += (double)tiles_per_state(pbs[i]->n) * batch[i] * (double)plans[i].passes.size();
+        longest = std::max(longest, (int)plans[i].passes.size());
+    }
+    const uint64_t tpc = (uint64_t)many_tiles_per_chunk(one_tile_items, longest, opt, c128);
     size_t off = 0;
     M.params = off;
     off += align_up(poff * sizeof(double));
@@ -1207,7 +1217,7 @@ qq_status plan_many(int count, qq_problem *const *pbs, const int *p, const int *
                 G.bytes += (double)pb->dim * diag_bytes_of(pb->diag_type);
             } else {
                 I.shift = c128 ? 0.0 : pb->alpha;  // the complex64 pass bodies accumulate with C - alpha
-                I.tpc = many_tiles_per_chunk(I.tiles, opt, c128);
+                I.tpc = (int)std::min(tpc, I.tiles);
                 I.nchunks = (int)((I.tiles + (uint64_t)I.tpc - 1) / (uint64_t)I.tpc);
                 I.npasses = (int)plan.passes.size();
                 int slot_base = 0;
@@ -1280,7 +1290,7 @@ qq_status plan_many(int count, qq_problem *const *pbs, const int *p, const int *
         G.total = (uint32_t)ticket;
         // workspace regions of the group
         G.ctl = off;
-        off += align_up((size_t)(2 + G.nstates) * sizeof(uint32_t));
+        off += align_up((size_t)(2 + G.nstates) * kCtlStride * sizeof(uint32_t));
         G.inst_off = 0;
         G.pass_off = align_up(G.inst.size() * sizeof(ManyInst), 16);
         G.seg_off = G.pass_off + align_up(G.pass.size() * sizeof(ManyPass), 16);
@@ -2433,7 +2443,7 @@ static qq_status evaluate_many_impl(int count, qq_problem *const *problems, cons
         QQ_HIP(hipMemcpyAsync(ws + G.desc, blob.data(), G.desc_bytes, hipMemcpyHostToDevice, stream));
     }
     for (ManyGroup &G : M.groups) {
-        QQ_HIP(launch_fill_u32(reinterpret_cast<uint32_t *>(ws + G.ctl), 0u, (size_t)(2 + G.nstates), stream));
+        QQ_HIP(launch_fill_u32(reinterpret_cast<uint32_t *>(ws + G.ctl), 0u, (size_t)(2 + G.nstates) * kCtlStride, stream));
         ManyArgs a;
         a.inst = reinterpret_cast<const ManyInst *>(ws + G.desc + G.inst_off);
         a.pass = reinterpret_cast<const ManyPass *>(ws + G.desc + G.pass_off);
@@ -2468,7 +2478,7 @@ static qq_status evaluate_many_impl(int count, qq_problem *const *problems, cons
     // error flags (and host outputs)
     std::vector<uint32_t> flags_h(M.groups.size(), 0);
     for (size_t gi = 0; gi < M.groups.size(); ++gi)
-        QQ_HIP(hipMemcpyAsync(&flags_h[gi], ws + M.groups[gi].ctl + sizeof(uint32_t), sizeof(uint32_t),
+        QQ_HIP(hipMemcpyAsync(&flags_h[gi], ws + M.groups[gi].ctl + kCtlStride * sizeof(uint32_t), sizeof(uint32_t),
                               hipMemcpyDeviceToHost, stream));
     std::vector<double> h;
     if (!(flags & QQ_OUT_ON_DEVICE)) {

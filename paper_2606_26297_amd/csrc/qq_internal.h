@@ -248,6 +248,10 @@ struct ManySeg {
     uint32_t first;  // ticket of chunk 0
     uint32_t inst, b, pass;
 };
+// Control words lie kCtlStride apart, one per cache line: tickets, polls and completions of different
+// states then do not queue behind each other (side by side they held the launch to ten items per
+// microsecond: 512 problems at one tile per item 93 ms against 35.7).
+constexpr int kCtlStride = 32;
 struct ManyArgs {
     const ManyInst *inst;
     const ManyPass *pass;
@@ -256,7 +260,7 @@ struct ManyArgs {
     int nseg;
     int grad;
     uint32_t total;       // tickets
-    uint32_t *ctl;        // [0] ticket head, [1] error flag, [2 + s] items completed for state s
+    uint32_t *ctl;        // word 0: ticket head, 1: error flag, 2 + s: items completed for state s
     double *partial;
     uint64_t spin_ticks;  // bound on one dependency wait, in wall-clock ticks
 };

@@ -69,6 +69,24 @@ __device__ __forceinline__ void gst(uint64_t sbase, O voff, float2 x)
     __builtin_nontemporal_store(u, reinterpret_cast<uint64_t __attribute__((address_space(1))) *>(sbase + voff));
 }
 
+// State accesses of the persistent launch, where another XCD's workgroup may have written the amplitude in
+// the same launch: agent-scope (relaxed atomic) accesses, which go past the XCD's own L2, so that neither
+// side needs a cache write-back or invalidate (see qq_many.hip).
+template <typename O>
+__device__ __forceinline__ float2 gld_coh(uint64_t sbase, O voff)
+{
+    const uint64_t u = __hip_atomic_load(reinterpret_cast<const uint64_t __attribute__((address_space(1))) *>(sbase + voff),
+                                         __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return make_float2(__uint_as_float((uint32_t)u), __uint_as_float((uint32_t)(u >> 32)));
+}
+template <typename O>
+__device__ __forceinline__ void gst_coh(uint64_t sbase, O voff, float2 x)
+{
+    const uint64_t u = (uint64_t)__float_as_uint(x.x) | ((uint64_t)__float_as_uint(x.y) << 32);
+    __hip_atomic_store(reinterpret_cast<uint64_t __attribute__((address_space(1))) *>(sbase + voff), u, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Two registers through one 16-byte access per lane.  In the thread layouts qubit 0 is lane bit 0, so
 // the two lanes of a lane pair hold neighbouring amplitudes: for registers (r, r + 1) the even lane
 // accesses register r's amplitudes z and z + 1, the odd lane register r + 1's, and one swap of 8 bytes
@@ -666,8 +684,8 @@ __device__ __forceinline__ void pass_body(const FastArgs &a, float2 *lds, double
     // wherever the lane offsets are (not WIDE).  Measured at n = 28, B = 64: mid 45.2 -> 43.7 ms,
     // adjoint mid 90.7 -> 87.8, last with the seed 52.0 -> 50.5, but the adjoint turn on the high sets
     // 94.0 / 95.4 -> 99 / 102.5 and the turn mixed (one set faster, one slower): so the 12-qubit set's
-    // passes and the last pass take them, the other high-set passes keep 8-byte accesses.  PR = false:
-    // never (the persistent launch: 22.0 -> 23.2 ms on the uneven batch with them)
+    // passes and the last pass take them, the other high-set passes keep 8-byte accesses.  PR = false
+    // (the persistent launch): never, and agent-scope accesses
     constexpr bool PAIR = PR && !WIDE && !PART && (!HIGH || KIND == FK_LASTG);
     const uint32_t odd = PAIR ? lane_lo & 1u : 0u;
     const uint32_t pv2 = PAIR ? vs2 - 8u * odd + odd * (uint32_t)(8ull << s8) : 0u;
@@ -713,11 +731,23 @@ __device__ __forceinline__ void pass_body(const FastArgs &a, float2 *lds, double
         auto cz_ready = [&](RegCost &rc) {
             if constexpr (TAB) reg_cost_form(rc, tv);
         };
-        auto ld2 = [&](uint64_t arr, int r) { return gld<float2>(arr + (sb2 + r * ss2) * 8, vs2); };
+        auto ld2 = [&](uint64_t arr, int r) {
+            const uint64_t at = arr + (sb2 + r * ss2) * 8;
+            if constexpr (PR) return gld<float2>(at, vs2);
+            else return gld_coh(at, vs2);
+        };
         // stores take their own opaque copy of the stride: sharing the load addresses
         // would keep 16-32 scalar address pairs live across the whole tile
-        auto st2f = [&](uint64_t arr, int r, float2 x, uint64_t ss) { gst(arr + (sb2 + r * ss) * 8, vs2, x); };
-        auto st1f = [&](uint64_t arr, int r, float2 x, uint64_t ss) { gst(arr + (sb1 + r * ss) * 8, vs1, x); };
+        auto st2f = [&](uint64_t arr, int r, float2 x, uint64_t ss) {
+            const uint64_t at = arr + (sb2 + r * ss) * 8;
+            if constexpr (PR) gst(at, vs2, x);
+            else gst_coh(at, vs2, x);
+        };
+        auto st1f = [&](uint64_t arr, int r, float2 x, uint64_t ss) {
+            const uint64_t at = arr + (sb1 + r * ss) * 8;
+            if constexpr (PR) gst(at, vs1, x);
+            else gst_coh(at, vs1, x);
+        };
         // all 16 registers of one state: loads in layout 2, stores in layout 2 / layout 1
         auto ld2all = [&](uint64_t arr, float2 (&x)[kRegs]) {
             if constexpr (PAIR) {
