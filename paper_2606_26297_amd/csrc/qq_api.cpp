@@ -155,9 +155,6 @@ struct qq_problem {
     // the pass kernels: regq[16 q + r] = sum over the bits k > j of r of b_{R_j R_k}, j the lowest
     // bit of r (0 for r = 0 and single bits); q = 0 .. n - 4.
     double *d_regq = nullptr;
-    // The same sums per factor of the partitioned phase (set by qq_set_allocation): [factor][q][16],
-    // factors 0 .. M-1 the QPU-local couplings, factor M the cross-QPU couplings.
-    double *d_part_cq = nullptr;
     // summary
     double alpha = 0, sigma_c = 0, cmin = 0, cmax = 0;
     uint64_t argmin = 0;
@@ -165,10 +162,16 @@ struct qq_problem {
     int num_qpus = 0;
     std::vector<int32_t> qpu;
     int64_t cross_terms = -1;
+    // each QPU's local table by its own variables' bits (complex64, and the one-tile evaluations), and the
+    // pair sums of regq per factor, [factor][q][16], factors 0 .. M-1 the QPU-local couplings,
+    // factor M the cross-QPU couplings
     int32_t *d_qpu = nullptr;
     void *d_tables = nullptr;
-    void *d_cross = nullptr;
     PartDesc *d_part = nullptr;
+    double *d_part_cq = nullptr;
+    // the diagonal of the cross-QPU couplings (n <= kTelegateMaxN: the one-tile evaluations and the
+    // gate-level trajectory)
+    void *d_cross = nullptr;
     // schedules pinned by qq_set_schedule / qq_autotune, keyed by (p, batch, planning flags)
     struct Sched {
         int p, batch, flags, G, pairing, blocked, set_order;
@@ -187,20 +190,21 @@ struct qq_problem {
         const double *rows, *thr;  // device
     };
     std::vector<CostTab> ctabs;
-    // the same tables of the cross-QPU couplings alone (qq_set_allocation), read by the partitioned phases
-    std::vector<CostTab> xtabs;
-    DevBuf xtab_buf, xthr_buf;
+    // the same tables of the QPU-local terms (linear ones and the constant among them) and of the cross-QPU
+    // couplings (qq_set_allocation), read by the partitioned phases (complex128 both, complex64 the cross part's)
+    std::vector<CostTab> ltabs, xtabs;
+    DevBuf ltab_buf, xtab_buf, xthr_buf;  // xthr_buf: both forms' per-thread constants
 
     ~qq_problem()
     {
-        void *ptrs[] = {d_part_cq, d_qpu, d_tables, d_cross, d_part};
+        void *ptrs[] = {d_qpu, d_tables, d_cross, d_part, d_part_cq};
         if (dim) (void)hipSetDevice(device);
         for (void *q : ptrs)
             if (q) (void)hipFree(q);
         // evaluations on the caller's streams may still read the handle's memory
         if (diag_buf.p && hipDeviceSynchronize() == hipSuccess)
-            for (DevBuf *b : {&diag_buf, &coef_buf, &ctab_buf, &xtab_buf, &xthr_buf}) b->done();
-        for (DevBuf *b : {&diag_buf, &coef_buf, &ctab_buf, &xtab_buf, &xthr_buf}) b->release();
+            for (DevBuf *b : {&diag_buf, &coef_buf, &ctab_buf, &ltab_buf, &xtab_buf, &xthr_buf}) b->done();
+        for (DevBuf *b : {&diag_buf, &coef_buf, &ctab_buf, &ltab_buf, &xtab_buf, &xthr_buf}) b->release();
         if (counted) pool_problem_removed(device);
     }
 };
@@ -475,11 +479,10 @@ int choose_G(int n, int B)
 // interleaved by 2^16); n = 32 with four QPUs, partitioned: 592 -> 565 ms.
 constexpr int kIlvBit = 16;
 
-// Whether the specialised kernels of the precision run this plan's passes.
-bool fast_plan(const qq_problem *pb, const Plan &plan, int flags)
+// Whether the specialised kernels run this plan's passes (every multi-pass plan).
+bool fast_plan(const qq_problem *pb, const Plan &plan)
 {
-    if (plan.sets.size() < 2 || pb->n > kFastMaxN) return false;
-    return !((flags & QQ_C128) && (flags & QQ_PARTITIONED));
+    return plan.sets.size() > 1 && pb->n <= kFastMaxN;
 }
 
 struct Layout {
@@ -701,8 +704,7 @@ qq_status run_plan(qq_problem *pb, const Plan &plan, const Layout &L, int p, int
     const size_t es = c128 ? 16 : 8;
     (void)es;
     if (plan.nslots > kMaxSlots) return fail(QQ_E_UNSUPPORTED, "plan needs %d accumulator slots (max %d)", plan.nslots, kMaxSlots);
-    // The specialised kernels serve every multi-pass plan but the partitioned complex128 ones.
-    const bool use_fast = fast_plan(pb, plan, flags);
+    const bool use_fast = fast_plan(pb, plan);
     // a single pass (n <= 12, one workgroup per set) writes the results itself
     const bool single = plan.sets.size() == 1;
     const double escale = pb->n < kTileBits ? std::ldexp(1.0, pb->n - kTileBits) : 1.0;
@@ -753,7 +755,8 @@ qq_status run_plan(qq_problem *pb, const Plan &plan, const Layout &L, int p, int
         if (use_fast && pp.fkind >= 0) {
             FastPassParams fp;
             fp.blocked = L.blocked;
-            fp.part = (flags & QQ_PARTITIONED) ? 1 : 0;
+            fp.part = (flags & QQ_PARTITIONED) &&
+                      (pp.fkind == FK_FIRST || pp.fkind == FK_TURN || pp.fkind == FK_BTURN) ? 1 : 0;
             fp.part_desc = pb->d_part;
             fp.part_tables = pb->d_tables;
             fp.B = B;
@@ -788,10 +791,12 @@ qq_status run_plan(qq_problem *pb, const Plan &plan, const Layout &L, int p, int
             if (!ct) return fail(QQ_E_DEVICE, "no cost table for the set at qubits %d / %d", sd.pos4, sd.pos8);
             fp.ctab = ct->rows;
             fp.cthr = ct->thr;
-            fp.xtab = fp.xthr = nullptr;
+            fp.ltab = fp.lthr = fp.xtab = fp.xthr = nullptr;
             if (fp.part) {
-                const auto *xt = find_table(pb->xtabs, sd, lane_q);
-                if (!xt) return fail(QQ_E_DEVICE, "no cross table for the set at qubits %d / %d", sd.pos4, sd.pos8);
+                const auto *lt = find_table(pb->ltabs, sd, lane_q), *xt = find_table(pb->xtabs, sd, lane_q);
+                if (!lt || !xt) return fail(QQ_E_DEVICE, "no partition tables for the set at qubits %d / %d", sd.pos4, sd.pos8);
+                fp.ltab = lt->rows;
+                fp.lthr = lt->thr;
                 fp.xtab = xt->rows;
                 fp.xthr = xt->thr;
             }
@@ -1810,18 +1815,18 @@ qq_status qq_set_allocation(qq_problem *pb, int M, const int32_t *qpu_of_var, co
             return fail(QQ_E_ALLOCATION, "QPU %d holds %d variables, capacity %d", m, count[m], capacities[m]);
     }
     int64_t cross = 0;
-    std::vector<int32_t> xij;
-    std::vector<double> xb;
-    std::vector<int32_t> xbi;
+    // couplings across QPUs (x) and within one (l), row-major
+    std::vector<int32_t> xij, xbi, lij;
+    std::vector<double> xb, lb;
     for (size_t k = 0; k < pb->pair_b.size(); ++k) {
         const int i = pb->pair_ij[2 * k], j = pb->pair_ij[2 * k + 1];
-        if (qpu_of_var[i] != qpu_of_var[j]) {
-            ++cross;
-            xij.push_back(i);
-            xij.push_back(j);
-            xb.push_back(pb->pair_b[k]);
-            xbi.push_back(pb->pair_bi[k]);
-        }
+        const bool across = qpu_of_var[i] != qpu_of_var[j];
+        auto &ij = across ? xij : lij;
+        ij.push_back(i);
+        ij.push_back(j);
+        (across ? xb : lb).push_back(pb->pair_b[k]);
+        if (across) xbi.push_back(pb->pair_bi[k]);
+        cross += across;
     }
     PartDesc pd;
     std::memset(&pd, 0, sizeof pd);
@@ -1837,8 +1842,9 @@ qq_status qq_set_allocation(qq_problem *pb, int M, const int32_t *qpu_of_var, co
         total += 1ull << pd.nvars[m];
     }
     const int es = diag_bytes_of(pb->diag_type);
-    if (qq_status st = check_device_fits(pb->device, (size_t)pb->dim * es * 2 + 2 * cost_table_bytes(n),
-                                         "the cross-QPU diagonal and its tables");
+    const bool need_cross = n <= kTelegateMaxN;
+    if (qq_status st = check_device_fits(pb->device, (size_t)pb->dim * es * (need_cross ? 2 : 1) + 3 * cost_table_bytes(n),
+                                         "the cross-QPU diagonal and the tables");
         st != QQ_OK)
         return st;
     QQ_HIP(hipSetDevice(pb->device));
@@ -1846,19 +1852,19 @@ qq_status qq_set_allocation(qq_problem *pb, int M, const int32_t *qpu_of_var, co
     void *olds[] = {pb->d_qpu, pb->d_tables, pb->d_cross, pb->d_part, pb->d_part_cq};
     for (void *q : olds)
         if (q) QQ_HIP(hipFree(q));
+    pb->ltab_buf.release();
     pb->xtab_buf.release();
     pb->xthr_buf.release();
+    pb->ltabs.clear();
     pb->xtabs.clear();
-    pb->d_part_cq = nullptr;
     pb->d_qpu = nullptr;
     pb->d_tables = pb->d_cross = nullptr;
     pb->d_part = nullptr;
+    pb->d_part_cq = nullptr;
     pb->num_qpus = 0;
     hipStream_t stream = nullptr;
     QQ_HIP(hipMalloc((void **)&pb->d_qpu, sizeof(int32_t) * n));
     QQ_HIP(hipMalloc(&pb->d_tables, total * es));
-    if (hipMalloc(&pb->d_cross, (size_t)pb->dim * es) != hipSuccess)
-        return fail(QQ_E_NOMEM, "hipMalloc for the cross diagonal failed");
     QQ_HIP(hipMalloc((void **)&pb->d_part, sizeof(PartDesc)));
     {
         // pair sums of every factor among each run of four consecutive qubits (see d_part_cq)
@@ -1885,44 +1891,53 @@ qq_status qq_set_allocation(qq_problem *pb, int M, const int32_t *qpu_of_var, co
     QQ_HIP(launch_local_tables(n, pb->diag_type, pb->d_part, pb->d_ell, pb->d_ell_i, (int)pb->pair_b.size(),
                                pb->d_pair_ij, pb->d_pair_b, pb->d_pair_bi, pb->d_qpu, pb->c0, pb->c0_i, pb->d_tables,
                                total, stream));
-    // cross diagonal: the cost diagonal of the cross couplings alone (no linear terms, no constant)
     {
-        const int nx = (int)xb.size();
-        DevBuf zero_ell, zero_elli, dij, db, dbi;
-        QQ_HIP(zero_ell.get(pb->device, sizeof(double) * n));
-        QQ_HIP(zero_elli.get(pb->device, sizeof(int32_t) * n));
-        QQ_HIP(hipMemset(zero_ell.p, 0, sizeof(double) * n));
-        QQ_HIP(hipMemset(zero_elli.p, 0, sizeof(int32_t) * n));
-        QQ_HIP(dij.get(pb->device, sizeof(int32_t) * std::max(2, 2 * nx)));
-        QQ_HIP(db.get(pb->device, sizeof(double) * std::max(1, nx)));
-        QQ_HIP(dbi.get(pb->device, sizeof(int32_t) * std::max(1, nx)));
-        if (nx) {
-            QQ_HIP(hipMemcpy(dij.p, xij.data(), sizeof(int32_t) * 2 * nx, hipMemcpyHostToDevice));
-            QQ_HIP(hipMemcpy(db.p, xb.data(), sizeof(double) * nx, hipMemcpyHostToDevice));
-            QQ_HIP(hipMemcpy(dbi.p, xbi.data(), sizeof(int32_t) * nx, hipMemcpyHostToDevice));
-        }
-        QQ_HIP(launch_cost_diag(n, pb->diag_type, static_cast<double *>(zero_ell.p), static_cast<int32_t *>(zero_elli.p),
-                                nx, static_cast<int32_t *>(dij.p), static_cast<double *>(db.p),
-                                static_cast<int32_t *>(dbi.p), 0.0, 0, pb->d_cross, pb->dim, stream));
-        // and its per-tile tables (the partitioned phases of the complex64 kernels read these)
+        const int nx = (int)xb.size(), nl = (int)lb.size();
         const std::vector<double> zeros(n, 0.0);
-        auto BX = [&](int i, int j) {
-            if (qpu_of_var[i] == qpu_of_var[j]) return 0.0;
+        DevBuf zero_ell, zero_elli, dij, db, dbi, dlij, dlb;
+        auto put = [&](DevBuf &buf, const void *src, size_t bytes) -> hipError_t {
+            if (hipError_t e = buf.get(pb->device, std::max<size_t>(bytes, 16)); e != hipSuccess) return e;
+            return bytes ? hipMemcpy(buf.p, src, bytes, hipMemcpyHostToDevice) : hipSuccess;
+        };
+        QQ_HIP(put(zero_ell, zeros.data(), sizeof(double) * n));
+        QQ_HIP(put(zero_elli, zeros.data(), sizeof(int32_t) * n));
+        QQ_HIP(put(dij, xij.data(), sizeof(int32_t) * 2 * nx));
+        QQ_HIP(put(db, xb.data(), sizeof(double) * nx));
+        QQ_HIP(put(dbi, xbi.data(), sizeof(int32_t) * nx));
+        QQ_HIP(put(dlij, lij.data(), sizeof(int32_t) * 2 * nl));
+        QQ_HIP(put(dlb, lb.data(), sizeof(double) * nl));
+        // cross diagonal: the cost diagonal of the cross couplings alone (no linear terms, no constant)
+        if (need_cross) {
+            if (hipMalloc(&pb->d_cross, (size_t)pb->dim * es) != hipSuccess)
+                return fail(QQ_E_NOMEM, "hipMalloc for the cross diagonal failed");
+            QQ_HIP(launch_cost_diag(n, pb->diag_type, static_cast<double *>(zero_ell.p),
+                                    static_cast<int32_t *>(zero_elli.p), nx, static_cast<int32_t *>(dij.p),
+                                    static_cast<double *>(db.p), static_cast<int32_t *>(dbi.p), 0.0, 0, pb->d_cross,
+                                    pb->dim, stream));
+        }
+        // the tables of the two parts (the partitioned phases of n > 12)
+        auto B = [&](int i, int j, bool across) {
+            if ((qpu_of_var[i] != qpu_of_var[j]) != across) return 0.0;
             return i < j ? pb->b[(size_t)i * n + j] : pb->b[(size_t)j * n + i];
         };
-        pb->xtabs = cost_table_list(n);
-        const std::vector<double> thr = table_constants(pb->xtabs, zeros, BX);
-        if (!thr.empty()) {
-            QQ_HIP(pb->xthr_buf.get(pb->device, thr.size() * sizeof(double)));
-            QQ_HIP(hipMemcpy(pb->xthr_buf.p, thr.data(), thr.size() * sizeof(double), hipMemcpyHostToDevice));
-        }
+        pb->ltabs = pb->xtabs = cost_table_list(n);
+        std::vector<double> thr = table_constants(pb->ltabs, pb->ell, [&](int i, int j) { return B(i, j, false); });
+        const size_t xthr_at = thr.size();
+        const std::vector<double> xthr = table_constants(pb->xtabs, zeros, [&](int i, int j) { return B(i, j, true); });
+        thr.insert(thr.end(), xthr.begin(), xthr.end());
+        QQ_HIP(put(pb->xthr_buf, thr.data(), thr.size() * sizeof(double)));
+        const double *d_thr = static_cast<const double *>(pb->xthr_buf.p);
+        if (qq_status st = build_tables(pb->device, n, pb->d_ell, nl, static_cast<int32_t *>(dlij.p),
+                                        static_cast<double *>(dlb.p), pb->c0, pb->ltabs, pb->ltab_buf, d_thr, stream);
+            st != QQ_OK)
+            return st;
         if (qq_status st = build_tables(pb->device, n, static_cast<double *>(zero_ell.p), nx,
                                         static_cast<int32_t *>(dij.p), static_cast<double *>(db.p), 0.0, pb->xtabs,
-                                        pb->xtab_buf, static_cast<const double *>(pb->xthr_buf.p), stream);
+                                        pb->xtab_buf, d_thr + xthr_at, stream);
             st != QQ_OK)
             return st;
         QQ_HIP(hipDeviceSynchronize());
-        for (DevBuf *q : {&zero_ell, &zero_elli, &dij, &db, &dbi}) q->done();
+        for (DevBuf *q : {&zero_ell, &zero_elli, &dij, &db, &dbi, &dlij, &dlb}) q->done();
     }
     pb->num_qpus = M;
     pb->qpu.assign(qpu_of_var, qpu_of_var + n);
@@ -2070,7 +2085,7 @@ qq_status qq_telegate_state(qq_problem *pb, int p, const double *params, const d
     if (!pb || !params || !psi_out) return fail(QQ_E_INVALID, "problem / params / psi_out is NULL");
     if (p < 1 || p > QQ_MAX_P) return fail(QQ_E_INVALID, "p = %d outside [1, %d]", p, QQ_MAX_P);
     if (flags & ~QQ_OUT_ON_DEVICE) return fail(QQ_E_INVALID, "flags 0x%x: only QQ_OUT_ON_DEVICE applies", flags);
-    if (pb->num_qpus < 1 || !pb->d_cross) return fail(QQ_E_ALLOCATION, "no allocation set (qq_set_allocation)");
+    if (pb->num_qpus < 1) return fail(QQ_E_ALLOCATION, "no allocation set (qq_set_allocation)");
     if (pb->n > kTelegateMaxN) return fail(QQ_E_TOO_LARGE, "n = %d: the trajectory holds n + 2 qubits, n <= %d", pb->n, kTelegateMaxN);
     if (qq_status st = check_params_host(params, 2 * (size_t)p); st != QQ_OK) return st;
     // cross-QPU couplings, row-major (pairs are stored in that order)
@@ -2845,7 +2860,7 @@ qq_status qq_autotune(qq_problem *pb, int p, int batch, int flags, const char *c
     for (int pr = 0; pr < npair; ++pr)
         for (int G : Gs)
             if (qq_status st = time_one(pr, G, 0, so0); st != QQ_OK) return st;
-    if (fast_plan(pb, plan0, flags)) {  // the tile order only applies to the specialised multi-pass kernels
+    if (fast_plan(pb, plan0)) {  // the tile order only applies to the specialised multi-pass kernels
         const int pr = bestP;
         for (int G : g_candidates(bestG))
             if (qq_status st = time_one(pr, G, 1, so0); st != QQ_OK) return st;

@@ -8,7 +8,7 @@ namespace {
 using namespace dev;
 
 // One workgroup per (state b, workgroup slot g); FP64 partial sums per slot.
-template <int KIND, bool HIGH, bool FULL>
+template <int KIND, bool HIGH, bool FULL, bool PART>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(KIND >= FK_LASTG ? 2 : KIND == FK_MID ? 4 : 3)))
 fast_pass128(const p128::Args a)
 {
@@ -22,7 +22,7 @@ fast_pass128(const p128::Args a)
     block_coords(a.B, a.G, b, g);
     double acc[3] = {0.0, 0.0, 0.0};
     const p128::Coef f = p128::coef<KIND>(a.params + (size_t)b * 2 * a.p, a.k);
-    p128::pass_body<KIND, HIGH, FULL>(a, lds, acc, t, b, g, f);
+    p128::pass_body<KIND, HIGH, FULL, PART>(a, lds, acc, t, b, g, f);
 
     if constexpr (NSLOT > 0) {
         const int lane = t & 63, wave = t >> 6;
@@ -59,14 +59,25 @@ single128(const SingleArgs a)
                               });
 }
 
-template <int KIND>
-hipError_t launch_kind(const p128::Args &a, bool high, hipStream_t s)
+template <int KIND, bool HIGH, bool FULL>
+hipError_t launch_geom(const p128::Args &a, bool part, hipStream_t s)
 {
     const dim3 grid((unsigned)(a.B * a.G)), block(kThreads);
-    if (!high) hipLaunchKernelGGL((fast_pass128<KIND, false, true>), grid, block, 0, s, a);
-    else if (a.active == 0x0ff0) hipLaunchKernelGGL((fast_pass128<KIND, true, true>), grid, block, 0, s, a);
-    else hipLaunchKernelGGL((fast_pass128<KIND, true, false>), grid, block, 0, s, a);
+    if constexpr (KIND == FK_FIRST || KIND == FK_TURN || KIND == FK_BTURN) {
+        if (part) {
+            hipLaunchKernelGGL((fast_pass128<KIND, HIGH, FULL, true>), grid, block, 0, s, a);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((fast_pass128<KIND, HIGH, FULL, false>), grid, block, 0, s, a);
     return hipGetLastError();
+}
+
+template <int KIND>
+hipError_t launch_kind(const p128::Args &a, bool high, bool part, hipStream_t s)
+{
+    if (!high) return launch_geom<KIND, false, true>(a, part, s);
+    return a.active == 0x0ff0 ? launch_geom<KIND, true, true>(a, part, s) : launch_geom<KIND, true, false>(a, part, s);
 }
 
 }  // namespace
@@ -100,15 +111,19 @@ hipError_t launch_fast_pass128(int kind, bool high, const FastPassParams &pp, hi
     a.cq = pp.cq;
     a.ctab = pp.ctab;
     a.cthr = pp.cthr;
+    a.ltab = pp.ltab;
+    a.lthr = pp.lthr;
+    a.xtab = pp.xtab;
+    a.xthr = pp.xthr;
     switch (kind) {
-    case FK_FIRST: return launch_kind<FK_FIRST>(a, high, s);
-    case FK_MID: return launch_kind<FK_MID>(a, high, s);
-    case FK_TURN: return launch_kind<FK_TURN>(a, high, s);
-    case FK_LAST: return launch_kind<FK_LAST>(a, high, s);
-    case FK_LASTG: return launch_kind<FK_LASTG>(a, high, s);
-    case FK_BMID: return launch_kind<FK_BMID>(a, high, s);
-    case FK_BTURN: return launch_kind<FK_BTURN>(a, high, s);
-    case FK_BLAST: return launch_kind<FK_BLAST>(a, high, s);
+    case FK_FIRST: return launch_kind<FK_FIRST>(a, high, pp.part != 0, s);
+    case FK_MID: return launch_kind<FK_MID>(a, high, pp.part != 0, s);
+    case FK_TURN: return launch_kind<FK_TURN>(a, high, pp.part != 0, s);
+    case FK_LAST: return launch_kind<FK_LAST>(a, high, pp.part != 0, s);
+    case FK_LASTG: return launch_kind<FK_LASTG>(a, high, pp.part != 0, s);
+    case FK_BMID: return launch_kind<FK_BMID>(a, high, pp.part != 0, s);
+    case FK_BTURN: return launch_kind<FK_BTURN>(a, high, pp.part != 0, s);
+    case FK_BLAST: return launch_kind<FK_BLAST>(a, high, pp.part != 0, s);
     default: return hipErrorInvalidValue;
     }
 }

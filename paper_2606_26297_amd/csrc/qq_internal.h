@@ -170,18 +170,21 @@ struct FastPassParams {
     int part_cq_runs;
     double shift;  // centre of the cost for the accumulations (the mean of C)
     // per-tile cost table of the layout in which the pass reads the cost ([tiles][kCostRow]) and the
-    // per-thread constants ([256][8]) that follow it; required by every non-partitioned pass kind that
+    // per-thread constants ([256][8]); required by every non-partitioned pass kind that
     // reads the cost
     const double *ctab;
     const double *cthr;
-    // the same for the cross-QPU couplings alone; required by the partitioned phases
+    // the same for the QPU-local terms together (complex128) and for the cross-QPU couplings; required by
+    // the partitioned phases
+    const double *ltab;
+    const double *lthr;
     const double *xtab;
     const double *xthr;
     int ilv;  // 0, or K: psi and lambda in alternating blocks of 2^K amplitudes (see Layout::ilv)
 };
 hipError_t launch_fast_pass(int kind, bool high, int diag_type, const FastPassParams &pp, hipStream_t s);
-// The same passes on complex128 states (qq_fast128.hip): monolithic phases, costs from the tables,
-// accumulations with C itself (no shift).
+// The same passes on complex128 states (qq_fast128.hip): every cost from the tables, accumulations with C
+// itself (no shift).
 hipError_t launch_fast_pass128(int kind, bool high, const FastPassParams &pp, hipStream_t s);
 
 // Whole complex128 evaluations of a problem with n <= 12, one workgroup per parameter set; results

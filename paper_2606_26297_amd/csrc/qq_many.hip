@@ -433,10 +433,10 @@ __device__ __forceinline__ void run_geom128(int geom, const p128::Args &a, doubl
     using W = typename std::conditional<kind_states<KIND>() == 2, double2, double>::type;
     W *l = reinterpret_cast<W *>(lds);
     if (geom == 0) {
-        p128::pass_body<KIND, false, true>(a, l, acc, t, b, g, f);
+        p128::pass_body<KIND, false, true, false>(a, l, acc, t, b, g, f);
     } else if constexpr (KIND != FK_FIRST) {  // the persistent plans take the qubit-0..11 set first
-        if (geom == 1) p128::pass_body<KIND, true, true>(a, l, acc, t, b, g, f);
-        else p128::pass_body<KIND, true, false>(a, l, acc, t, b, g, f);
+        if (geom == 1) p128::pass_body<KIND, true, true, false>(a, l, acc, t, b, g, f);
+        else p128::pass_body<KIND, true, false, false>(a, l, acc, t, b, g, f);
     }
 }
 
@@ -468,6 +468,7 @@ __device__ __forceinline__ void run_chunk128(const ManyInst &I, const ManyPass &
     a.cq = I.regq + 16 * (P.kind == FK_FIRST ? P.pos8 : P.pos4);
     a.ctab = P.ctab;
     a.cthr = P.cthr;
+    a.ltab = a.lthr = a.xtab = a.xthr = nullptr;  // no partitioned phases here
     double acc[3] = {0.0, 0.0, 0.0};
     const int g = (int)t0;
     switch (P.kind) {

@@ -221,6 +221,7 @@ struct Args {
     const double *cq;
     const double *ctab;
     const double *cthr;
+    const double *ltab, *lthr, *xtab, *xthr;  // PART: the QPU-local parts' and the cross part's
 };
 
 // The layer constants of a pass: (cos, sin) of the first and the second mixer, gamma of its phase.
@@ -256,7 +257,10 @@ __device__ __forceinline__ Coef coef(const double *x, int k)
 }
 
 // The tile loop of one pass kind (the kinds' operations are listed in qq_passes.h).
-template <int KIND, bool HIGH, bool FULL, typename W>
+// PART: phases by the QPU-local parts together and the cross part, one rotation by the sum of their two
+// quadratic forms (the operation-list kernel took a gathered read, a sine and a cosine per QPU and amplitude:
+// n = 20, eight sets, three QPUs, p = 3, gradient 3.62 -> 0.79 ms).
+template <int KIND, bool HIGH, bool FULL, bool PART, typename W>
 __device__ __forceinline__ void pass_body(const Args &a, W *lds, double (&acc)[3], int t, int b, int g,
                                           const Coef &f)
 {
@@ -287,9 +291,23 @@ __device__ __forceinline__ void pass_body(const Args &a, W *lds, double (&acc)[3
         const uint64_t ss2 = opaque_u64(1ull << a.pos8), ss1 = opaque_u64(1ull << a.pos4);
         const uint64_t sb2 = base + w2, sb1 = base + w1;
         RegQ *cq = (RegQ *)a.cq;
-        TabVals tv;
+        TabVals tv, xv;
         RegCost rc;
-        auto tab = [&]() { tab_load(tv, a.ctab + tile * kCostRow, a.cthr + 8 * t, t, wave); };
+        auto tab = [&]() {
+            tab_load(tv, (PART ? a.ltab : a.ctab) + tile * kCostRow, (PART ? a.lthr : a.cthr) + 8 * t, t, wave);
+            if constexpr (PART) tab_load(xv, a.xtab + tile * kCostRow, a.xthr + 8 * t, t, wave);
+        };
+        auto form = [&]() {
+            if constexpr (PART) {
+                tv.lane += xv.lane;
+                tv.wave += xv.wave;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) tv.reg[j] += xv.reg[j];
+#pragma unroll
+                for (int j = 0; j < 5; ++j) tv.thr[j] += xv.thr[j];
+            }
+            reg_cost_form(rc, tv);
+        };
         auto load = [&](uint64_t arr, double2 (&x)[kRegs]) {
 #pragma unroll
             for (int r = 0; r < kRegs; ++r) x[r] = gld<O1>(arr + (sb2 + r * ss2) * 16, vs2);
@@ -307,7 +325,7 @@ __device__ __forceinline__ void pass_body(const Args &a, W *lds, double (&acc)[3
         double unused = 0.0;
         if constexpr (KIND == FK_FIRST) {
             tab();
-            reg_cost_form(rc, tv);
+            form();
 #pragma unroll
             for (int r = 0; r < kRegs; ++r) {
                 double c, s;
@@ -324,7 +342,7 @@ __device__ __forceinline__ void pass_body(const Args &a, W *lds, double (&acc)[3
             if constexpr (KIND == FK_MID) {
                 store1(psi_a, v[0]);
             } else if constexpr (KIND == FK_TURN) {
-                reg_cost_form(rc, tv);
+                form();
 #pragma unroll
                 for (int r = 0; r < kRegs; ++r) {
                     double c, s;
@@ -335,7 +353,7 @@ __device__ __forceinline__ void pass_body(const Args &a, W *lds, double (&acc)[3
                 mix_op<HIGH, FULL, 1, 1, 1, false>(lds, v, t, a.active, f.c2, f.s2, unused);
                 store2(psi_a, v[0]);
             } else {
-                reg_cost_form(rc, tv);
+                form();
                 double e = 0.0;
 #pragma unroll
                 for (int r = 0; r < kRegs; ++r)
@@ -347,7 +365,7 @@ __device__ __forceinline__ void pass_body(const Args &a, W *lds, double (&acc)[3
             load(psi_a, v[0]);
             tab();
             mix_op<HIGH, FULL, 2, 2, 1, false>(lds, v, t, a.active, f.c1, f.s1, unused);
-            reg_cost_form(rc, tv);
+            form();
             double e = 0.0;
 #pragma unroll
             for (int r = 0; r < kRegs; ++r) {
@@ -367,7 +385,7 @@ __device__ __forceinline__ void pass_body(const Args &a, W *lds, double (&acc)[3
                 store1(psi_a, v[0]);
                 store1(lam_a, v[1]);
             } else {
-                reg_cost_form(rc, tv);
+                form();
                 double gg = 0.0;
 #pragma unroll
                 for (int r = 0; r < kRegs; ++r) {

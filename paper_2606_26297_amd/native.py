@@ -778,7 +778,8 @@ def kernel_name(rec) -> str:
     if rec["pass_kind"] >= 0:
         tf = lambda x: "true" if x else "false"  # noqa: E731
         if rec["c128"]:
-            return f"fast_pass128<{rec['pass_kind']}, {tf(rec['high'])}, {tf(rec['full'])}>"
+            return (f"fast_pass128<{rec['pass_kind']}, {tf(rec['high'])}, {tf(rec['full'])}, "
+                    f"{tf(rec.get('part'))}>")
         name = "fast_pass_part" if rec.get("part") else "fast_pass"
         if rec["high"] and not rec["full"] and rec["n"] >= 32:  # 64-bit lane offsets
             return f"{name}_wide<{rec['pass_kind']}, {dt}>"

@@ -67,3 +67,26 @@ def test_c128_matches_the_oracle(kind, n, p, scale):
                 assert np.max(np.abs(v - gr)[0::2]) <= 4 * float(cmax) ** 2 * s, (v, gr)
     finally:
         pb.close()
+
+
+@pytest.mark.parametrize("kind", ["int16", "real"])
+@pytest.mark.parametrize("n,p,qpus", [(9, 2, 2), (13, 3, 3), (17, 2, 4), (21, 2, 5)])
+def test_c128_partitioned_matches_the_oracle(kind, n, p, qpus):
+    """Partitioned phases (interleaved variables, so that every run of qubits spans several QPUs): the same
+    unitary, within the same bound (the two forms' values carry the roundings of one each)."""
+    q = instance(kind, n, 60 + n)
+    pb = Problem(q.H, q.f, q.c0)
+    x = W.random_params(p, 2, 70 + n)
+    try:
+        pb.set_allocation([i % qpus for i in range(n)], qpus)
+        e, g = pb.evaluate(x, grad=True, c128=True, partitioned=True)
+        d = O.cost_diagonal(q.H, q.f, q.c0)
+        cmax = float(np.max(np.abs(d)))
+        for b in range(2):
+            er, gr = O.gradient(d, x[b])
+            s = 2 * state_bound(n, x[b], d)
+            assert abs(e[b] - er) <= 2 * cmax * s
+            assert np.max(np.abs(g[b] - gr)[1::2]) <= 4 * n * cmax * s
+            assert np.max(np.abs(g[b] - gr)[0::2]) <= 4 * cmax**2 * s
+    finally:
+        pb.close()
