@@ -2185,7 +2185,8 @@ qq_status qq_sample(qq_problem *pb, int p, const double *params, int flags, int6
     const bool c128 = flags & QQ_C128;
     const uint64_t nblk = std::max<uint64_t>(1, pb->dim >> kTileBits);
     const size_t o_start = align_up(nblk * sizeof(double)), o_u = o_start + align_up((nblk + 1) * sizeof(double)),
-                 o_out = o_u + (dev_in ? 0 : align_up((size_t)shots * sizeof(double))),
+                 o_after = o_u + (dev_in ? 0 : align_up((size_t)shots * sizeof(double))),
+                 o_top = o_after + align_up(nblk * 64 * sizeof(double)), o_out = o_top + align_up(nblk * 64 * sizeof(double)),
                  total = o_out + (dev_out ? 0 : align_up((size_t)shots * sizeof(uint64_t)));
     DevBuf buf;
     if (buf.get(pb->device, total) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) for the shots failed", total);
@@ -2195,7 +2196,8 @@ qq_status qq_sample(qq_problem *pb, int p, const double *params, int flags, int6
     uint64_t *d_out = dev_out ? indices_out : reinterpret_cast<uint64_t *>(b + o_out);
     if (!dev_in)
         QQ_HIP(hipMemcpyAsync(b + o_u, uniforms, (size_t)shots * sizeof(double), hipMemcpyHostToDevice, stream));
-    QQ_HIP(launch_block_mass(psi, c128, pb->dim, nblk, d_mass, stream));
+    double *d_after = reinterpret_cast<double *>(b + o_after), *d_top = reinterpret_cast<double *>(b + o_top);
+    QQ_HIP(launch_block_mass(psi, c128, pb->dim, nblk, d_mass, d_after, d_top, stream));
     // prefix over the block masses in index order (host, sequential FP64)
     std::vector<double> h(nblk), start(nblk + 1);
     QQ_HIP(hipMemcpyAsync(h.data(), d_mass, nblk * sizeof(double), hipMemcpyDeviceToHost, stream));
@@ -2207,7 +2209,7 @@ qq_status qq_sample(qq_problem *pb, int p, const double *params, int flags, int6
         if (h[i] > 0.0) last_blk = i;
     }
     QQ_HIP(hipMemcpyAsync(d_start, start.data(), (nblk + 1) * sizeof(double), hipMemcpyHostToDevice, stream));
-    QQ_HIP(launch_shots(psi, c128, pb->dim, nblk, d_start, last_blk, d_u, shots, d_out, stream));
+    QQ_HIP(launch_shots(psi, c128, pb->dim, nblk, d_start, last_blk, d_after, d_top, d_u, shots, d_out, stream));
     if (!dev_out)
         QQ_HIP(hipMemcpyAsync(indices_out, d_out, (size_t)shots * sizeof(uint64_t), hipMemcpyDeviceToHost, stream));
     QQ_HIP(hipStreamSynchronize(stream));

@@ -300,88 +300,70 @@ __device__ __forceinline__ bool better(double p1, uint64_t i1, double p2, uint64
     return p1 > p2 || (p1 == p2 && i1 < i2);
 }
 
-struct TopList {
-    double p[kTopK];
-    uint64_t i[kTopK];
-    __device__ void init()
+// A wave's best k in registers spread over its lanes: lane j holds the j-th best, in the order of
+// `better`; tp, ti: the k-th best (wave-uniform).
+struct WaveList {
+    double lp = -1.0, tp = -1.0;
+    uint64_t li = ~0ull, ti = ~0ull;
+
+    // Offer one entry per lane (where valid).  An entry is a candidate only if it beats the k-th best;
+    // candidates are inserted one at a time (a wave-uniform loop over their ballot).
+    __device__ __forceinline__ void offer(double pz, uint64_t z, bool valid, int lane, int k)
     {
-#pragma unroll
-        for (int k = 0; k < kTopK; ++k) {
-            p[k] = -1.0;
-            i[k] = ~0ull;
+        uint64_t m = __ballot(valid && better(pz, z, tp, ti));
+        while (m) {
+            const int src = __ffsll((unsigned long long)m) - 1;
+            m &= m - 1;
+            const double xp = __shfl(pz, src);
+            const uint64_t xi = __shfl(z, src);
+            if (!better(xp, xi, tp, ti)) continue;  // overtaken by an insertion of this chunk
+            const int pos = __popcll(__ballot(lane < k && better(lp, li, xp, xi)));
+            const double up = __shfl_up(lp, 1);
+            const uint64_t ui = __shfl_up(li, 1);
+            if (lane == pos) {
+                lp = xp;
+                li = xi;
+            } else if (lane > pos) {
+                lp = up;
+                li = ui;
+            }
+            tp = __shfl(lp, k - 1);
+            ti = __shfl(li, k - 1);
         }
     }
-    __device__ void insert(double pp, uint64_t ii)
+
+    // The workgroup's best k from its four wave lists: put(rank, p, i) by the lane of wave 0 that holds the
+    // entry.  An entry's rank is the number of entries better than it (ties between empty entries broken by
+    // position, so ranks are distinct).
+    template <typename Put>
+    __device__ __forceinline__ void merge(int lane, int wave, int k, Put put)
     {
-        if (!better(pp, ii, p[kTopK - 1], i[kTopK - 1])) return;
-        p[kTopK - 1] = pp;
-        i[kTopK - 1] = ii;
-#pragma unroll
-        for (int k = kTopK - 1; k > 0; --k) {
-            if (better(p[k], i[k], p[k - 1], i[k - 1])) {
-                const double tp = p[k];
-                p[k] = p[k - 1];
-                p[k - 1] = tp;
-                const uint64_t ti = i[k];
-                i[k] = i[k - 1];
-                i[k - 1] = ti;
-            }
+        __shared__ double sp[4 * kTopK];
+        __shared__ uint64_t si[4 * kTopK];
+        if (lane < k) {
+            sp[wave * k + lane] = lp;
+            si[wave * k + lane] = li;
+        }
+        __syncthreads();
+        if (wave == 0 && lane < 4 * k) {
+            const double mp = sp[lane];
+            const uint64_t mi = si[lane];
+            int rank = 0;
+            for (int j = 0; j < 4 * k; ++j)
+                rank += (better(sp[j], si[j], mp, mi) || (j < lane && sp[j] == mp && si[j] == mi)) ? 1 : 0;
+            if (rank < k) put(rank, mp, mi);
         }
     }
 };
 
-// k rounds of a workgroup tournament over the per-thread sorted lists.
-__device__ void tournament(TopList &L, int k, double *outp, uint64_t *outi)
-{
-    __shared__ double sp[256];
-    __shared__ uint64_t si[256];
-    __shared__ int sw[256];
-    const int t = threadIdx.x;
-    int head = 0;
-    for (int round = 0; round < k; ++round) {
-        double hp = -1.0;
-        uint64_t hi = ~0ull;
-#pragma unroll
-        for (int q = 0; q < kTopK; ++q)
-            if (q == head) {
-                hp = L.p[q];
-                hi = L.i[q];
-            }
-        sp[t] = hp;
-        si[t] = hi;
-        sw[t] = t;
-        __syncthreads();
-        for (int w = 128; w >= 1; w >>= 1) {
-            if (t < w && better(sp[t + w], si[t + w], sp[t], si[t])) {
-                sp[t] = sp[t + w];
-                si[t] = si[t + w];
-                sw[t] = sw[t + w];
-            }
-            __syncthreads();
-        }
-        if (t == 0) {
-            outp[round] = sp[0];
-            outi[round] = si[0];
-        }
-        if (sw[0] == t) ++head;
-        __syncthreads();
-    }
-}
-
-// Stage 1 of the top-k: the best k (probability, index) pairs of each workgroup's amplitudes.  Each
-// wave keeps its own best k in registers spread over its lanes (lane j holds the j-th best, in the
-// order of `better`), and an amplitude is a candidate only if it beats the wave's current k-th best.
-// A wave sees its amplitudes in an order unrelated to their probabilities, so after the first few
-// chunks candidates are rare: most of the sweep is a load, |psi|^2 and one comparison per amplitude,
-// and the insertions (a wave-uniform loop over the ballot of candidates) are taken one at a time.
+// Stage 1 of the top-k: the best k (probability, index) pairs of each workgroup's amplitudes.  A wave sees
+// its amplitudes in an order unrelated to their probabilities, so after the first few chunks candidates
+// are rare: most of the sweep is a load, |psi|^2 and one comparison per amplitude.
 template <typename C2>
 __global__ void __launch_bounds__(256) topk_stage1(const C2 *psi, uint64_t dim, int k, double *cp, uint64_t *ci)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    double lp = -1.0;      // this lane's entry of the wave's list (j-th best for lane j < k)
-    uint64_t li = ~0ull;
-    double tp = -1.0;      // the wave's current k-th best (wave-uniform)
-    uint64_t ti = ~0ull;
+    WaveList L;
     constexpr int kUnroll = 8;
     const uint64_t stride = (uint64_t)gridDim.x * blockDim.x;
     // the loop runs over wave-uniform bases so that every lane takes part in the ballots and shuffles
@@ -397,67 +379,42 @@ __global__ void __launch_bounds__(256) topk_stage1(const C2 *psi, uint64_t dim, 
             const uint64_t z = zb + lane + u * stride;
             const bool valid = z < dim;
             const double re = valid ? (double)v[u].x : 0.0, im = valid ? (double)v[u].y : 0.0;
-            const double pz = valid ? fma(re, re, im * im) : -1.0;
-            uint64_t m = __ballot(valid && better(pz, z, tp, ti));
-            while (m) {
-                const int src = __ffsll((unsigned long long)m) - 1;
-                m &= m - 1;
-                const double xp = __shfl(pz, src);
-                const uint64_t xi = __shfl(z, src);
-                if (!better(xp, xi, tp, ti)) continue;  // overtaken by an insertion of this chunk
-                const int pos = __popcll(__ballot(lane < k && better(lp, li, xp, xi)));
-                const double up = __shfl_up(lp, 1);
-                const uint64_t ui = __shfl_up(li, 1);
-                if (lane == pos) {
-                    lp = xp;
-                    li = xi;
-                } else if (lane > pos) {
-                    lp = up;
-                    li = ui;
-                }
-                tp = __shfl(lp, k - 1);
-                ti = __shfl(li, k - 1);
-            }
+            L.offer(valid ? fma(re, re, im * im) : -1.0, z, valid, lane, k);
         }
     }
-    // the workgroup's best k from the four wave lists: each candidate's rank is the number of
-    // candidates better than it (ties between empty entries broken by position, so ranks are distinct)
-    __shared__ double sp[4 * kTopK];
-    __shared__ uint64_t si[4 * kTopK];
-    if (lane < k) {
-        sp[wave * k + lane] = lp;
-        si[wave * k + lane] = li;
-    }
-    __syncthreads();
-    if (wave == 0 && lane < 4 * k) {
-        const double mp = sp[lane];
-        const uint64_t mi = si[lane];
-        int rank = 0;
-        for (int j = 0; j < 4 * k; ++j)
-            rank += (better(sp[j], si[j], mp, mi) || (j < lane && sp[j] == mp && si[j] == mi)) ? 1 : 0;
-        if (rank < k) {
-            cp[(size_t)blockIdx.x * k + rank] = mp;
-            ci[(size_t)blockIdx.x * k + rank] = mi;
-        }
-    }
+    L.merge(lane, wave, k, [&](int rank, double p, uint64_t i) {
+        cp[(size_t)blockIdx.x * k + rank] = p;
+        ci[(size_t)blockIdx.x * k + rank] = i;
+    });
 }
 
+// Stage 2: the best k of the workgroups' lists, one workgroup, the same wave lists.  Eight candidates per
+// lane are loaded together; the serial part is the insertions, a few dozen per wave (a sorted list per
+// thread and k rounds of a workgroup tournament took 58 us for 1024 lists of ten).
 template <typename DT>
 __global__ void __launch_bounds__(256) topk_stage2(const double *cp, const uint64_t *ci, int ncand, int k,
                                                     const DT *diag, uint64_t *oi, double *op, double *oc)
 {
-    __shared__ double fp[kTopK];
-    __shared__ uint64_t fi[kTopK];
-    TopList L;
-    L.init();
-    for (int e = threadIdx.x; e < ncand; e += blockDim.x) L.insert(cp[e], ci[e]);
-    tournament(L, k, fp, fi);
-    __syncthreads();
-    if (threadIdx.x < k) {
-        oi[threadIdx.x] = fi[threadIdx.x];
-        op[threadIdx.x] = fp[threadIdx.x];
-        oc[threadIdx.x] = (double)diag[fi[threadIdx.x]];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    WaveList L;
+    constexpr int kUnroll = 8;
+    for (int e0 = wave * 64; e0 < ncand; e0 += 256 * kUnroll) {
+        double p[kUnroll];
+        uint64_t i[kUnroll];
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) {
+            const int e = e0 + lane + 256 * u;
+            p[u] = e < ncand ? cp[e] : -1.0;
+            i[u] = e < ncand ? ci[e] : ~0ull;
+        }
+#pragma unroll
+        for (int u = 0; u < kUnroll; ++u) L.offer(p[u], i[u], e0 + lane + 256 * u < ncand, lane, k);
     }
+    L.merge(lane, wave, k, [&](int rank, double p, uint64_t i) {
+        oi[rank] = i;
+        op[rank] = p;
+        oc[rank] = (double)diag[i];
+    });
 }
 
 template <typename R, int NS>
