@@ -21,6 +21,7 @@
 
 #include "qq_internal.h"
 #include "qq_pool.h"
+#include "qq_tables.h"
 
 using namespace qq;
 
@@ -635,44 +636,28 @@ size_t cost_table_bytes(int n)
     return cost_table_list(n).size() * ((size_t)tiles_per_state(n) * kCostRow + 256 * 8) * sizeof(double);
 }
 
-// Per-thread constants of the tables of one quadratic cost c0 + sum l_i z_i + sum_{i<j} b_ij z_i z_j
-// (see qq_problem::CostTab), [table][256][8]: P(E) and l_Rj + sum_{q in E} b_q,Rj, with E the thread's
-// lane and wave bits.
-template <typename BF>
-std::vector<double> table_constants(const std::vector<qq_problem::CostTab> &tabs, const std::vector<double> &ell, BF B)
+// The runs of a problem's tables (at most two per set of three pairings).
+qq_status table_runs(const std::vector<qq_problem::CostTab> &tabs, TableRuns &r)
 {
-    std::vector<double> thr(256 * 8 * tabs.size(), 0.0);
+    if (tabs.size() > sizeof r.lane_q / sizeof r.lane_q[0]) return fail(QQ_E_UNSUPPORTED, "%zu cost tables", tabs.size());
+    r.count = (int)tabs.size();
     for (size_t k = 0; k < tabs.size(); ++k) {
-        const qq_problem::CostTab &tb = tabs[k];
-        const int lq = tb.lane_q, rq = lq == tb.pos4 ? tb.pos8 : tb.pos4;
-        const int eq[8] = {0, 1, 2, 3, lq, lq + 1, lq + 2, lq + 3};
-        for (int t = 0; t < 256; ++t) {
-            double P = 0.0;
-            for (int a = 0; a < 8; ++a) {
-                if (!((t >> a) & 1)) continue;
-                P += ell[eq[a]];
-                for (int c = a + 1; c < 8; ++c)
-                    if ((t >> c) & 1) P += B(eq[a], eq[c]);
-            }
-            double *row = &thr[(k * 256 + t) * 8];
-            row[0] = P;
-            for (int j = 0; j < 4; ++j) {
-                double q = ell[rq + j];
-                for (int a = 0; a < 8; ++a)
-                    if ((t >> a) & 1) q += B(eq[a], rq + j);
-                row[1 + j] = q;
-            }
-        }
+        r.lane_q[k] = tabs[k].lane_q;
+        r.reg_q[k] = tabs[k].lane_q == tabs[k].pos4 ? tabs[k].pos8 : tabs[k].pos4;
     }
-    return thr;
+    return QQ_OK;
 }
 
-// The tables' rows, computed on the device into `buf`; d_thr holds the per-thread constants.
-qq_status build_tables(int device, int n, const double *d_ell, int np, const int32_t *d_pij, const double *d_pb,
-                       double c0, std::vector<qq_problem::CostTab> &tabs, DevBuf &buf, const double *d_thr,
-                       hipStream_t stream)
+// The tables of one quadratic cost c0 + sum l_i z_i + sum_{i<j} b_ij z_i z_j (see qq_problem::CostTab) from the
+// device's linear terms, symmetric matrix b and pair list: rows into `buf`, per-thread constants into d_thr.
+qq_status build_tables(int device, int n, const double *d_ell, const double *d_b, int np, const int32_t *d_pij,
+                       const double *d_pb, double c0, std::vector<qq_problem::CostTab> &tabs, DevBuf &buf,
+                       double *d_thr, hipStream_t stream)
 {
     if (tabs.empty()) return QQ_OK;
+    TableRuns runs{};
+    if (qq_status st = table_runs(tabs, runs); st != QQ_OK) return st;
+    QQ_HIP(launch_table_constants(n, runs, d_ell, d_b, d_thr, stream));
     const uint64_t T = tiles_per_state(n);
     const size_t per = (size_t)T * kCostRow, need = per * tabs.size() * sizeof(double);
     if (buf.get(device, need) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) for the cost tables failed", need);
@@ -1647,7 +1632,7 @@ qq_status qq_problem_create(int n, const double *H, const double *f, double c0, 
     pb->d_diag = pb->diag_buf.p;
     pb->counted = true;
     pool_problem_added(device);
-    // the coefficient lists, the register-run sums and the tables' per-thread constants: one block, one copy
+    // the coefficient lists and the register-run sums (one copy) and the tables' per-thread constants: one block
     std::vector<double> regq(16 * (size_t)std::max(1, n - 3), 0.0);
     for (int q = 0; q + 4 <= n; ++q)
         for (int r = 1; r < 16; ++r) {
@@ -1658,9 +1643,9 @@ qq_status qq_problem_create(int n, const double *H, const double *f, double c0, 
             regq[16 * (size_t)q + r] = sum;
         }
     pb->ctabs = cost_table_list(n);
-    const std::vector<double> thr = table_constants(pb->ctabs, pb->ell, [&](int i, int j) {
-        return i < j ? pb->b[(size_t)i * n + j] : pb->b[(size_t)j * n + i];
-    });
+    std::vector<double> bsym((size_t)n * n, 0.0);
+    for (int i = 0; i < n; ++i)
+        for (int j = i + 1; j < n; ++j) bsym[(size_t)i * n + j] = bsym[(size_t)j * n + i] = pb->b[(size_t)i * n + j];
     std::vector<char> host;
     auto put = [&](const void *src, size_t bytes) {
         const size_t at = align_up(host.size());
@@ -1671,8 +1656,8 @@ qq_status qq_problem_create(int n, const double *H, const double *f, double c0, 
     const size_t o_ell = put(pb->ell.data(), sizeof(double) * n), o_elli = put(pb->ell_i.data(), sizeof(int32_t) * n),
                  o_pij = put(pb->pair_ij.data(), sizeof(int32_t) * 2 * np), o_pb = put(pb->pair_b.data(), sizeof(double) * np),
                  o_pbi = put(pb->pair_bi.data(), sizeof(int32_t) * np), o_regq = put(regq.data(), sizeof(double) * regq.size()),
-                 o_thr = put(thr.data(), sizeof(double) * thr.size());
-    QQ_HIP(pb->coef_buf.get(device, host.size()));
+                 o_b = put(bsym.data(), sizeof(double) * bsym.size()), o_thr = align_up(host.size());
+    QQ_HIP(pb->coef_buf.get(device, o_thr + 256 * 8 * sizeof(double) * pb->ctabs.size()));
     char *coef = static_cast<char *>(pb->coef_buf.p);
     QQ_HIP(hipMemcpyAsync(coef, host.data(), host.size(), hipMemcpyHostToDevice, stream));
     pb->d_ell = reinterpret_cast<double *>(coef + o_ell);
@@ -1685,8 +1670,9 @@ qq_status qq_problem_create(int n, const double *H, const double *f, double c0, 
         return launch_cost_diag(n, pb->diag_type, pb->d_ell, pb->d_ell_i, np, pb->d_pair_ij, pb->d_pair_b,
                                 pb->d_pair_bi, c0, pb->c0_i, pb->d_diag, pb->dim, stream);
     }));
-    if (qq_status st = build_tables(device, n, pb->d_ell, np, pb->d_pair_ij, pb->d_pair_b, c0, pb->ctabs, pb->ctab_buf,
-                                    reinterpret_cast<const double *>(coef + o_thr), stream);
+    if (qq_status st = build_tables(device, n, pb->d_ell, reinterpret_cast<const double *>(coef + o_b), np, pb->d_pair_ij,
+                                    pb->d_pair_b, c0, pb->ctabs, pb->ctab_buf, reinterpret_cast<double *>(coef + o_thr),
+                                    stream);
         st != QQ_OK)
         return st;
 
@@ -1916,28 +1902,32 @@ qq_status qq_set_allocation(qq_problem *pb, int M, const int32_t *qpu_of_var, co
                                     pb->dim, stream));
         }
         // the tables of the two parts (the partitioned phases of n > 12)
-        auto B = [&](int i, int j, bool across) {
-            if ((qpu_of_var[i] != qpu_of_var[j]) != across) return 0.0;
+        auto B = [&](int i, int j) {
             return i < j ? pb->b[(size_t)i * n + j] : pb->b[(size_t)j * n + i];
         };
         pb->ltabs = pb->xtabs = cost_table_list(n);
-        std::vector<double> thr = table_constants(pb->ltabs, pb->ell, [&](int i, int j) { return B(i, j, false); });
-        const size_t xthr_at = thr.size();
-        const std::vector<double> xthr = table_constants(pb->xtabs, zeros, [&](int i, int j) { return B(i, j, true); });
-        thr.insert(thr.end(), xthr.begin(), xthr.end());
-        QQ_HIP(put(pb->xthr_buf, thr.data(), thr.size() * sizeof(double)));
-        const double *d_thr = static_cast<const double *>(pb->xthr_buf.p);
-        if (qq_status st = build_tables(pb->device, n, pb->d_ell, nl, static_cast<int32_t *>(dlij.p),
-                                        static_cast<double *>(dlb.p), pb->c0, pb->ltabs, pb->ltab_buf, d_thr, stream);
+        std::vector<double> bl((size_t)n * n, 0.0), bx((size_t)n * n, 0.0);
+        for (int i = 0; i < n; ++i)
+            for (int j = 0; j < n; ++j)
+                if (i != j) (qpu_of_var[i] == qpu_of_var[j] ? bl : bx)[(size_t)i * n + j] = B(i, j);
+        DevBuf dbl, dbx;
+        QQ_HIP(put(dbl, bl.data(), sizeof(double) * bl.size()));
+        QQ_HIP(put(dbx, bx.data(), sizeof(double) * bx.size()));
+        const size_t nthr = 256 * 8 * pb->ltabs.size();
+        QQ_HIP(pb->xthr_buf.get(pb->device, std::max<size_t>(16, 2 * nthr * sizeof(double))));
+        double *d_thr = static_cast<double *>(pb->xthr_buf.p);
+        if (qq_status st = build_tables(pb->device, n, pb->d_ell, static_cast<double *>(dbl.p), nl,
+                                        static_cast<int32_t *>(dlij.p), static_cast<double *>(dlb.p), pb->c0, pb->ltabs,
+                                        pb->ltab_buf, d_thr, stream);
             st != QQ_OK)
             return st;
-        if (qq_status st = build_tables(pb->device, n, static_cast<double *>(zero_ell.p), nx,
-                                        static_cast<int32_t *>(dij.p), static_cast<double *>(db.p), 0.0, pb->xtabs,
-                                        pb->xtab_buf, d_thr + xthr_at, stream);
+        if (qq_status st = build_tables(pb->device, n, static_cast<double *>(zero_ell.p), static_cast<double *>(dbx.p),
+                                        nx, static_cast<int32_t *>(dij.p), static_cast<double *>(db.p), 0.0, pb->xtabs,
+                                        pb->xtab_buf, d_thr + nthr, stream);
             st != QQ_OK)
             return st;
         QQ_HIP(hipDeviceSynchronize());
-        for (DevBuf *q : {&zero_ell, &zero_elli, &dij, &db, &dbi, &dlij, &dlb}) q->done();
+        for (DevBuf *q : {&zero_ell, &zero_elli, &dij, &db, &dbi, &dlij, &dlb, &dbl, &dbx}) q->done();
     }
     pb->num_qpus = M;
     pb->qpu.assign(qpu_of_var, qpu_of_var + n);

@@ -19,6 +19,7 @@
 
 #include "qq_device.h"
 #include "qq_generic.h"
+#include "qq_tables.h"
 
 namespace qq {
 namespace {
@@ -84,6 +85,14 @@ struct alignas(4 * sizeof(T)) Quad {
     T v[4];
 };
 
+// Lane l's value, in scalar registers.
+__device__ __forceinline__ int32_t lane_of(int32_t x, int l) { return __builtin_amdgcn_readlane(x, l); }
+__device__ __forceinline__ double lane_of(double x, int l)
+{
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l),
+                            __builtin_amdgcn_readlane(__double2loint(x), l));
+}
+
 template <bool INT, typename DT>
 __global__ void __launch_bounds__(256) cost_diag_kernel(int n, uint64_t dim, const double *ell, const int32_t *ell_i,
                                                          int npairs, const int32_t *pij, const double *pb,
@@ -112,10 +121,24 @@ __global__ void __launch_bounds__(256) cost_diag_kernel(int n, uint64_t dim, con
     if (threadIdx.x == 0)
         for (int r = n - 1; r >= 0; --r) s_rows[r] = min(s_rows[r], s_rows[r + 1]);
     __syncthreads();
-    // lane r holds the first pair of row r; read with readlane (no memory latency in the row loop)
-    const int vrows = s_rows[min((int)(threadIdx.x & 63), n)];
+    // lane r holds the first pair of row r and the linear term r, lane k the pair k of the chunk of 64 pairs
+    // in hand; the loops read them with readlane, so no memory latency sits in the chain of additions
+    // (scalar loads per term took a dense n = 18 diagonal 31 us, whatever its size)
+    const int lane = threadIdx.x & 63;
+    const int vrows = s_rows[min(lane, n)];
+    const Acc vell = lane < n ? (INT ? (Acc)ell_i[lane] : (Acc)ell[lane]) : (Acc)0;
+    int chunk = -1, cj = 0;
+    Acc cw = 0;
+    auto pair_chunk = [&](int k) {
+        if ((k >> 6) == chunk) return;
+        chunk = k >> 6;
+        const int kk = min(64 * chunk + lane, npairs - 1);
+        cj = pij[2 * kk + 1];
+        cw = INT ? (Acc)pbi[kk] : (Acc)pb[kk];
+    };
+    if (npairs > 0) pair_chunk(0);
 
-    const uint32_t lo = 4u * (uint32_t)(threadIdx.x & 63);
+    const uint32_t lo = 4u * (uint32_t)lane;
     const uint64_t nw = (uint64_t)gridDim.x * (blockDim.x >> 6);
     for (uint64_t w = uni64((uint64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6)); (w << kLow) < dim;
          w += nw) {
@@ -125,7 +148,7 @@ __global__ void __launch_bounds__(256) cost_diag_kernel(int n, uint64_t dim, con
         for (int u = 0; u < 4; ++u) acc[u] = INT ? (Acc)c0_i : (Acc)c0;
         for (int i = 0; i < n; ++i) {
             const int iu = __builtin_amdgcn_readfirstlane(i);
-            const Acc l = INT ? (Acc)ell_i[iu] : (Acc)ell[iu];
+            const Acc l = lane_of(vell, iu);
             if (iu < kLow) {
 #pragma unroll
                 for (int u = 0; u < 4; ++u) acc[u] = (((lo + u) >> iu) & 1u) ? acc[u] + l : acc[u];
@@ -145,8 +168,9 @@ __global__ void __launch_bounds__(256) cost_diag_kernel(int n, uint64_t dim, con
 
                 for (int k = k0; k < k1; ++k) {
                     const int ku = __builtin_amdgcn_readfirstlane(k);
-                    const int j = pij[2 * ku + 1];
-                    const Acc wv = INT ? (Acc)pbi[ku] : (Acc)pb[ku];
+                    pair_chunk(ku);
+                    const int j = __builtin_amdgcn_readlane(cj, ku & 63);
+                    const Acc wv = lane_of(cw, ku & 63);
                     const Acc wu = ((zb >> j) & 1ull) ? wv : neutral;
 #pragma unroll
                     for (int u = 0; u < 4; ++u) acc[u] += wu;
@@ -156,8 +180,9 @@ __global__ void __launch_bounds__(256) cost_diag_kernel(int n, uint64_t dim, con
 
                 for (int k = k0; k < k1; ++k) {
                     const int ku = __builtin_amdgcn_readfirstlane(k);
-                    const int j = pij[2 * ku + 1];
-                    const Acc wv = INT ? (Acc)pbi[ku] : (Acc)pb[ku];
+                    pair_chunk(ku);
+                    const int j = __builtin_amdgcn_readlane(cj, ku & 63);
+                    const Acc wv = lane_of(cw, ku & 63);
                     const uint32_t hj = (uint32_t)((zb >> j) & 1ull);
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
@@ -513,7 +538,45 @@ __global__ void __launch_bounds__(256) cost_table_kernel(int n, int high, int po
     else if (lane < 8) row[64 + lane] = lane == 4 ? G[8] : lane == 5 ? G[9] : lane == 6 ? G[10] : G[11];
 }
 
+// One workgroup per table, one thread per row; the sums in the order of the bits (a table's constants took the
+// host 256 x 70 additions and a copy of 16 KB).
+__global__ void __launch_bounds__(256) table_constants_kernel(int n, const TableRuns runs, const double *ell,
+                                                               const double *b, double *out)
+{
+    __shared__ double s_b[12][12], s_l[12];
+    const int t = threadIdx.x, lq = runs.lane_q[blockIdx.x], rq = runs.reg_q[blockIdx.x];
+    // the 12 qubits of the tile: 0..3, the lane run, the register run
+    auto qubit = [&](int i) { return i < 4 ? i : i < 8 ? lq + i - 4 : rq + i - 8; };
+    if (t < 144) s_b[t / 12][t % 12] = b[qubit(t / 12) * n + qubit(t % 12)];
+    if (t < 12) s_l[t] = ell[qubit(t)];
+    __syncthreads();
+    double P = 0.0;
+    for (int a = 0; a < 8; ++a) {
+        if (!((t >> a) & 1)) continue;
+        P += s_l[a];
+        for (int c = a + 1; c < 8; ++c)
+            if ((t >> c) & 1) P += s_b[a][c];
+    }
+    double *row = out + ((size_t)blockIdx.x * 256 + t) * 8;
+    row[0] = P;
+    for (int j = 0; j < 4; ++j) {
+        double q = s_l[8 + j];
+        for (int a = 0; a < 8; ++a)
+            if ((t >> a) & 1) q += s_b[a][8 + j];
+        row[1 + j] = q;
+    }
+    for (int j = 5; j < 8; ++j) row[j] = 0.0;
+}
+
 }  // namespace
+
+hipError_t launch_table_constants(int n, const TableRuns &runs, const double *ell, const double *b, double *out,
+                                  hipStream_t s)
+{
+    if (runs.count < 1) return hipSuccess;
+    hipLaunchKernelGGL(table_constants_kernel, dim3((unsigned)runs.count), dim3(256), 0, s, n, runs, ell, b, out);
+    return hipGetLastError();
+}
 
 hipError_t launch_cost_table(int n, int high, int pos4, int pos8, int lane_q, int reg_q, uint64_t tiles,
                              const double *d_ell, int npairs, const int32_t *d_pair_ij, const double *d_pair_b,
