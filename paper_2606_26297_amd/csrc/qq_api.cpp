@@ -463,10 +463,13 @@ Plan make_plan(int n, int p, int mode, int pairing = 0, int set_order = 0)
 
 uint64_t tiles_per_state(int n) { return n <= kTileBits ? 1ull : (1ull << (n - kTileBits)); }
 
+// Workgroups per state: 16384 over the batch, which leaves a few tiles to each at the largest sizes and one
+// at the small ones.  Against 4096: n = 28, eight states, gradient 329 -> 322 ms; n = 20, 256 states, energies
+// 3.52 -> 3.39 ms; n = 27, two states, partitioned 12.42 -> 12.33; below 4096 tiles in all the same.
 int choose_G(int n, int B)
 {
     const uint64_t T = tiles_per_state(n);
-    uint64_t target = std::max<uint64_t>(1, 4096 / (uint64_t)B);
+    uint64_t target = std::max<uint64_t>(1, 16384 / (uint64_t)B);
     uint64_t G = 1;
     while (G * 2 <= target && G * 2 <= T) G *= 2;
     return (int)G;
@@ -2334,7 +2337,9 @@ qq_status qq_topk(qq_problem *pb, int p, const double *params, int flags, int k,
     Layout L;
     if (qq_status st = state_into(pb, p, params, flags, stream, own, L); st != QQ_OK) return st;
     const void *psi = static_cast<char *>(own.p) + L.psi;
-    const int nblocks = (int)std::min<uint64_t>(1024, (pb->dim + 255) / 256);
+    // 512 workgroups: every wave pays for the insertions of its first amplitudes, and stage 2 reads k candidates
+    // per workgroup (n = 24, the whole call: 128 workgroups 550 us, 256 513, 512 499, 1024 526)
+    const int nblocks = (int)std::min<uint64_t>(512, (pb->dim + 255) / 256);
     DevBuf scratch;
     const size_t sb = (size_t)nblocks * k * 16 + (size_t)k * 24 + 256;
     if (scratch.get(pb->device, sb) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc failed");
