@@ -1,6 +1,7 @@
 // qq_generic.h -- the general pass body: one pass's list of operations (mixer on any subset of the
 // tile bits, phase, energy, adjoint seed, gamma-derivative with un-phase) applied to tiles of one
-// state in complex64 or complex128, shared by the per-pass kernel and the persistent launch.
+// state in complex64 or complex128.  It serves the one-tile evaluations (n <= 12) that no specialised
+// kernel takes: complex64, and partitioned phases in either precision.
 //
 // The operations follow the QAOA state eq. (11): cost unitary eq. (10), mixer eq. (12)-(13); the
 // energy is eq. (15) and the adjoint sweep gives the gradient of eq. (17).
