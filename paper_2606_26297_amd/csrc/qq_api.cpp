@@ -490,7 +490,7 @@ bool fast_plan(const qq_problem *pb, const Plan &plan)
 }
 
 struct Layout {
-    size_t psi = 0, lam = 0, partial = 0, params = 0, out = 0, total = 0;
+    size_t psi = 0, lam = 0, partial = 0, params = 0, pre = 0, out = 0, total = 0;
     size_t stride = 0;  // amplitudes from one state's region to the next
     int ilv = 0;        // 0, or kIlvBit: psi and lambda interleaved in blocks of 2^kIlvBit amplitudes
     int G = 1;
@@ -526,6 +526,8 @@ Layout make_layout(const qq_problem *pb, int p, int B, int flags, const Plan &pl
     off += align_up((size_t)std::max(1, plan.nslots) * B * L.G * sizeof(double));
     L.params = off;
     off += align_up((size_t)B * 2 * p * sizeof(double));
+    L.pre = off;
+    if (multi) off += align_up((size_t)B * p * 16);
     L.out = off;
     off += align_up((size_t)B * (1 + 2 * p) * sizeof(double));
     L.total = off;
@@ -767,6 +769,7 @@ qq_status run_plan(qq_problem *pb, const Plan &plan, const Layout &L, int p, int
             fp.psi = a.psi;
             fp.lam = a.lam;
             fp.state_stride = L.stride;
+            fp.pre = ws + L.pre;
             fp.ilv = L.ilv;
             fp.partial = a.partial;
             fp.cq = pb->d_regq + 16 * (pp.fkind == FK_FIRST ? sd.pos8 : sd.pos4);

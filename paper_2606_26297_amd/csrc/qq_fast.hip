@@ -20,6 +20,10 @@ __device__ __forceinline__ void fast_pass_impl(const FastArgs &a)
     int b, g;
     block_coords(a.B, a.G, b, g);
     double acc[3] = {0.0, 0.0, 0.0};
+    if constexpr (KIND == FK_FIRST) {
+        // the later passes' layer coefficients, one thread per layer
+        if (g == 0 && t < a.p) a.pre[(size_t)b * a.p + t] = mix_pre(a.params[((size_t)b * a.p + t) * 2 + 1]);
+    }
     // the per-pass kernels form the cost values from the per-tile tables (non-partitioned phases)
     run_pass<KIND, HIGH, FULL, DT, PART, WIDE, !PART>(a, lds, acc, t, b, g);
 
@@ -174,6 +178,7 @@ hipError_t launch_fast_pass(int kind, bool high, int diag_type, const FastPassPa
     a.cthr = pp.cthr;
     a.xtab = pp.xtab;
     a.xthr = pp.xthr;
+    a.pre = static_cast<MixPre *>(pp.pre);
     a.ilv = pp.ilv;
     const bool part = pp.part != 0;
     switch (kind) {

@@ -21,7 +21,15 @@ fast_pass128(const p128::Args a)
     int b, g;
     block_coords(a.B, a.G, b, g);
     double acc[3] = {0.0, 0.0, 0.0};
-    const p128::Coef f = p128::coef<KIND>(a.params + (size_t)b * 2 * a.p, a.k);
+    if constexpr (KIND == FK_FIRST) {
+        // the later passes' layer coefficients, one thread per layer
+        if (g == 0 && t < a.p) {
+            double sb, cb;
+            sincos(a.params[((size_t)b * a.p + t) * 2 + 1], &sb, &cb);
+            a.pre[(size_t)b * a.p + t] = make_double2(cb, sb);
+        }
+    }
+    const p128::Coef f = p128::coef<KIND, true>(a, b);
     p128::pass_body<KIND, HIGH, FULL, PART>(a, lds, acc, t, b, g, f);
 
     if constexpr (NSLOT > 0) {
@@ -111,6 +119,7 @@ hipError_t launch_fast_pass128(int kind, bool high, const FastPassParams &pp, hi
     a.cq = pp.cq;
     a.ctab = pp.ctab;
     a.cthr = pp.cthr;
+    a.pre = static_cast<double2 *>(pp.pre);
     a.ltab = pp.ltab;
     a.lthr = pp.lthr;
     a.xtab = pp.xtab;

@@ -144,6 +144,14 @@ hipError_t launch_local_tables(int n, int diag_type, const PartDesc *d_pd, const
                                const int32_t *d_pair_bi, const int32_t *d_qpu, double c0, int32_t c0_i, void *d_tables,
                                uint64_t total, hipStream_t s);
 
+// Mixer coefficients of one layer in factored form, forwards (see qq_passes.h): m = tan beta (formB 0) or
+// cot beta (1) rounded to float, sigma the normalisation of that rounded value.  In complex128: (cos, sin).
+struct MixPre {
+    float m;
+    int formB;
+    double sigma;
+};
+
 // Specialised complex64 pass kernels (qq_fast.hip): one kernel per pass kind.
 enum FastPassKind : int { FK_FIRST = 0, FK_MID, FK_TURN, FK_LAST, FK_LASTG, FK_BMID, FK_BTURN, FK_BLAST, FK_SINGLE };
 struct FastPassParams {
@@ -180,6 +188,7 @@ struct FastPassParams {
     const double *lthr;
     const double *xtab;
     const double *xthr;
+    void *pre;  // [B][p] x 16 bytes of the workspace: layer coefficients, written by the first pass
     int ilv;  // 0, or K: psi and lambda in alternating blocks of 2^K amplitudes (see Layout::ilv)
 };
 hipError_t launch_fast_pass(int kind, bool high, int diag_type, const FastPassParams &pp, hipStream_t s);

@@ -265,6 +265,7 @@ __device__ __forceinline__ void run_chunk(const ManyInst &I, const ManyPass &P, 
     a.ctab = P.ctab;
     a.cthr = P.cthr;
     a.xtab = a.xthr = nullptr;  // no partitioned phases here
+    a.pre = nullptr;            // every item forms its own
     a.ilv = 0;                  // separate psi and lambda arrays
     double acc[3] = {0.0, 0.0, 0.0};
     const int g = (int)t0;
@@ -428,7 +429,7 @@ template <int KIND>
 __device__ __forceinline__ void run_geom128(int geom, const p128::Args &a, double2 *lds, double (&acc)[3], int t, int b,
                                             int g)
 {
-    const p128::Coef f = p128::coef<KIND>(a.params + (size_t)b * 2 * a.p, a.k);
+    const p128::Coef f = p128::coef<KIND, false>(a, b);
     // one-state kinds transpose in two rounds of 8-byte words (registers bound this kernel, not LDS)
     using W = typename std::conditional<kind_states<KIND>() == 2, double2, double>::type;
     W *l = reinterpret_cast<W *>(lds);
@@ -469,6 +470,7 @@ __device__ __forceinline__ void run_chunk128(const ManyInst &I, const ManyPass &
     a.ctab = P.ctab;
     a.cthr = P.cthr;
     a.ltab = a.lthr = a.xtab = a.xthr = nullptr;  // no partitioned phases here
+    a.pre = nullptr;                              // every item forms its own
     double acc[3] = {0.0, 0.0, 0.0};
     const int g = (int)t0;
     switch (P.kind) {

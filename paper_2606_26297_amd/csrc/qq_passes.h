@@ -216,29 +216,42 @@ struct MixCoef {
     double sig2;  // sigma^2
 };
 
-__device__ __forceinline__ MixCoef mix_coef(double beta, bool inverse, int nact)
+// The part of a layer's coefficients that depends on beta alone (MixPre, qq_internal.h).
+__device__ __forceinline__ MixPre mix_pre(double beta)
 {
     double s, c;
     sincos(beta, &s, &c);
-    MixCoef r;
-    double sigma;
+    MixPre r;
     if (fabs(c) >= fabs(s)) {
         const float t = (float)(s / c);
         r.formB = 0;
-        r.m = inverse ? -t : t;
-        sigma = copysign(1.0, c) / sqrt(fma((double)t, (double)t, 1.0));
+        r.m = t;
+        r.sigma = copysign(1.0, c) / sqrt(fma((double)t, (double)t, 1.0));
     } else {
         const float u = (float)(c / s);
         r.formB = 1;
-        r.m = inverse ? -u : u;
-        sigma = copysign(1.0, s) / sqrt(fma((double)u, (double)u, 1.0));
-        if (inverse) sigma = -sigma;
+        r.m = u;
+        r.sigma = copysign(1.0, s) / sqrt(fma((double)u, (double)u, 1.0));
     }
+    return r;
+}
+
+__device__ __forceinline__ MixCoef mix_from(const MixPre &q, bool inverse, int nact)
+{
+    MixCoef r;
+    r.formB = q.formB;
+    r.m = inverse ? -q.m : q.m;
+    const double sigma = inverse && q.formB ? -q.sigma : q.sigma;
     r.sig2 = sigma * sigma;
     double sc = 1.0;
     for (int i = 0; i < nact; ++i) sc *= sigma;
     r.scale = (float)sc;
     return r;
+}
+
+__device__ __forceinline__ MixCoef mix_coef(double beta, bool inverse, int nact)
+{
+    return mix_from(mix_pre(beta), inverse, nact);
 }
 
 // Scheduling fences between butterfly stages keep the stages in place (each
@@ -503,6 +516,8 @@ struct FastArgs {
     // the same for the cross-QPU couplings alone (partitioned phases)
     const double *xtab;
     const double *xthr;
+    // [B][p] (per-pass kernels): written by the first pass, read by the others
+    MixPre *pre;
     // 0: psi and lambda are separate arrays; K > 0: their blocks of 2^K amplitudes alternate (lambda's
     // block right after psi's), so index bit q >= K of a state sits at address bit q + 1
     int ilv;
@@ -970,24 +985,39 @@ __device__ __forceinline__ void run_pass(const FastArgs &a, float2 *lds, double 
     const double *x = a.params + (size_t)b * 2 * a.p;
     MixCoef c1{}, c2{};
     double gam = 0.0;
+    // the coefficients of layer k (wave-uniform): from the first pass's table in the per-pass kernels (a sine,
+    // a cosine, a division and a root in FP64 per layer and workgroup are 1 to 2 us of a 10 us launch at
+    // n = 16), formed here in the persistent launch and in the first pass
+    auto mix = [&](int k, bool inverse) {
+        if constexpr (PR && KIND != FK_FIRST) {
+            const auto *q = (const MixPre __attribute__((address_space(4))) *)(a.pre + (size_t)b * a.p + k);
+            MixPre r;
+            r.m = q->m;
+            r.formB = q->formB;
+            r.sigma = q->sigma;
+            return mix_from(r, inverse, a.nact);
+        } else {
+            return mix_coef(x[2 * k + 1], inverse, a.nact);
+        }
+    };
     if constexpr (KIND == FK_FIRST) {
         gam = x[0];
-        c1 = mix_coef(x[1], false, a.nact);
+        c1 = mix(0, false);
     } else if constexpr (KIND == FK_MID || KIND == FK_LAST) {
-        c1 = mix_coef(x[2 * a.k + 1], false, a.nact);
+        c1 = mix(a.k, false);
     } else if constexpr (KIND == FK_TURN) {
-        c1 = mix_coef(x[2 * a.k + 1], false, a.nact);
+        c1 = mix(a.k, false);
         gam = x[2 * (a.k + 1)];
-        c2 = mix_coef(x[2 * (a.k + 1) + 1], false, a.nact);
+        c2 = mix(a.k + 1, false);
     } else if constexpr (KIND == FK_LASTG) {
-        c1 = mix_coef(x[2 * a.k + 1], false, a.nact);
-        c2 = mix_coef(x[2 * a.k + 1], true, a.nact);
+        c1 = mix(a.k, false);
+        c2 = mix(a.k, true);
     } else if constexpr (KIND == FK_BMID || KIND == FK_BLAST) {
-        c1 = mix_coef(x[2 * a.k + 1], true, a.nact);
+        c1 = mix(a.k, true);
     } else if constexpr (KIND == FK_BTURN) {
-        c1 = mix_coef(x[2 * a.k + 1], true, a.nact);
+        c1 = mix(a.k, true);
         gam = x[2 * a.k];
-        c2 = mix_coef(x[2 * (a.k - 1) + 1], true, a.nact);
+        c2 = mix(a.k - 1, true);
     }
     const double g2pi = gam * QQ_INV_TWO_PI;
     constexpr bool TWO = KIND == FK_TURN || KIND == FK_LASTG || KIND == FK_BTURN;

@@ -221,6 +221,7 @@ struct Args {
     const double *cq;
     const double *ctab;
     const double *cthr;
+    double2 *pre;  // [B][p]: (cos, sin) of beta_k, written by the first pass (per-pass kernels)
     const double *ltab, *lthr, *xtab, *xthr;  // PART: the QPU-local parts' and the cross part's
 };
 
@@ -229,18 +230,30 @@ struct Coef {
     double c1, s1, c2, s2, gam;
 };
 
-template <int KIND>
-__device__ __forceinline__ Coef coef(const double *x, int k)
+// TABLE: from the first pass's (cos, sin) per layer (the first pass itself forms its own).
+template <int KIND, bool TABLE>
+__device__ __forceinline__ Coef coef(const Args &a, int b)
 {
+    const double *x = a.params + (size_t)b * 2 * a.p;
+    const int k = a.k;
+    auto cs = [&](int layer, double &c, double &s) {
+        if constexpr (TABLE && KIND != FK_FIRST) {
+            const auto *q = (const double __attribute__((address_space(4))) *)(a.pre + (size_t)b * a.p + layer);
+            c = q[0];
+            s = q[1];
+        } else {
+            sincos(x[2 * layer + 1], &s, &c);
+        }
+    };
     Coef f{};
     if constexpr (KIND == FK_FIRST) {
         f.gam = x[0];
-        sincos(x[1], &f.s1, &f.c1);
+        cs(0, f.c1, f.s1);
     } else {
-        sincos(x[2 * k + 1], &f.s1, &f.c1);
+        cs(k, f.c1, f.s1);
         if constexpr (KIND == FK_TURN) {
             f.gam = x[2 * (k + 1)];
-            sincos(x[2 * (k + 1) + 1], &f.s2, &f.c2);
+            cs(k + 1, f.c2, f.s2);
         } else if constexpr (KIND == FK_LASTG) {
             f.c2 = f.c1;
             f.s2 = -f.s1;
@@ -249,7 +262,7 @@ __device__ __forceinline__ Coef coef(const double *x, int k)
         } else if constexpr (KIND == FK_BTURN) {
             f.s1 = -f.s1;
             f.gam = x[2 * k];
-            sincos(x[2 * (k - 1) + 1], &f.s2, &f.c2);
+            cs(k - 1, f.c2, f.s2);
             f.s2 = -f.s2;
         }
     }
