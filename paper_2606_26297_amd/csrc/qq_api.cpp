@@ -526,10 +526,9 @@ Layout make_layout(const qq_problem *pb, int p, int B, int flags, const Plan &pl
     off += align_up((size_t)std::max(1, plan.nslots) * B * L.G * sizeof(double));
     L.params = off;
     off += align_up((size_t)B * 2 * p * sizeof(double));
-    L.pre = off;
-    if (multi) off += align_up((size_t)B * p * 16);
     L.out = off;
     off += align_up((size_t)B * (1 + 2 * p) * sizeof(double));
+    L.pre = L.out;  // the layer coefficients (16 B p bytes) are read before the reduction writes its results there
     L.total = off;
     return L;
 }
