@@ -37,12 +37,18 @@ using passes::u32x4;
 
 // exp(-i theta): theta reduced modulo pi/2 by a two-term Cody-Waite reduction with FMAs, then the Taylor
 // polynomials of sine (to x^17) and cosine (to x^16) on [-pi/4, pi/4], whose remainders there are below
-// 1e-19 and 3e-18.
+// 1e-19 and 3e-18.  The rounding of theta * 2 / pi leaves the remainder up to |theta| 2^-52 outside that
+// interval, so it is reduced once more (by j = 0, which changes nothing, up to about |theta| = 2^44; the low
+// part of j pi / 2 is below the first step's own rounding) and bounded; the result keeps modulus 1 for every
+// finite theta.  Straight-line: a branch to this step spills the two-state kinds.
 __device__ __forceinline__ void cos_sin(double th, double &c, double &s)
 {
     const double k = rint(th * (4.0 * QQ_INV_TWO_PI));
-    const double x = fma(-k, 0.25 * QQ_TWO_PI_LO, fma(-k, 0.25 * QQ_TWO_PI_HI, th));
-    const int q = (int)(k - 4.0 * rint(0.25 * k));  // k modulo 4, in -2..2
+    double x = fma(-k, 0.25 * QQ_TWO_PI_LO, fma(-k, 0.25 * QQ_TWO_PI_HI, th));
+    const double j = rint(x * (4.0 * QQ_INV_TWO_PI));
+    x = fma(-j, 0.25 * QQ_TWO_PI_HI, x);
+    x = fabs(x) > 0.8 ? 0.0 : x;  // beyond 2^96 or so; a NaN stays
+    const int q = (int)(k - 4.0 * rint(0.25 * k)) + (int)j;  // k + j modulo 4 in the low bits
     const double y = x * x;
     double ps = 1.0 / 355687428096000.0;
     ps = fma(ps, y, -1.0 / 1307674368000.0);
