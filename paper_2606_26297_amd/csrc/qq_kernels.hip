@@ -413,12 +413,13 @@ __global__ void __launch_bounds__(256) topk_stage1(const C2 *psi, uint64_t dim, 
     });
 }
 
-// Stage 2: the best k of the workgroups' lists, one workgroup, the same wave lists.  Eight candidates per
+// Stage 2: the best k of the workgroups' lists, one workgroup, the same wave lists; a rank that no amplitude
+// fills (NaN states compare with nothing) has no index and a NaN cost.  Eight candidates per
 // lane are loaded together; the serial part is the insertions, a few dozen per wave (a sorted list per
 // thread and k rounds of a workgroup tournament took 58 us for 1024 lists of ten).
 template <typename DT>
 __global__ void __launch_bounds__(256) topk_stage2(const double *cp, const uint64_t *ci, int ncand, int k,
-                                                    const DT *diag, uint64_t *oi, double *op, double *oc)
+                                                    uint64_t dim, const DT *diag, uint64_t *oi, double *op, double *oc)
 {
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     WaveList L;
@@ -438,7 +439,7 @@ __global__ void __launch_bounds__(256) topk_stage2(const double *cp, const uint6
     L.merge(lane, wave, k, [&](int rank, double p, uint64_t i) {
         oi[rank] = i;
         op[rank] = p;
-        oc[rank] = (double)diag[i];
+        oc[rank] = i < dim ? (double)diag[i] : __builtin_nan("");
     });
 }
 
@@ -669,15 +670,15 @@ hipError_t launch_topk(const void *psi, bool c128, uint64_t dim, int k, const vo
                            dim, k, cp, ci);
     switch (diag_type) {
     case DIAG_F64:
-        hipLaunchKernelGGL(topk_stage2<double>, dim3(1), dim3(256), 0, s, cp, ci, nblocks * k, k,
+        hipLaunchKernelGGL(topk_stage2<double>, dim3(1), dim3(256), 0, s, cp, ci, nblocks * k, k, dim,
                            static_cast<const double *>(diag), d_idx, d_prob, d_cost);
         break;
     case DIAG_I32:
-        hipLaunchKernelGGL(topk_stage2<int32_t>, dim3(1), dim3(256), 0, s, cp, ci, nblocks * k, k,
+        hipLaunchKernelGGL(topk_stage2<int32_t>, dim3(1), dim3(256), 0, s, cp, ci, nblocks * k, k, dim,
                            static_cast<const int32_t *>(diag), d_idx, d_prob, d_cost);
         break;
     default:
-        hipLaunchKernelGGL(topk_stage2<int16_t>, dim3(1), dim3(256), 0, s, cp, ci, nblocks * k, k,
+        hipLaunchKernelGGL(topk_stage2<int16_t>, dim3(1), dim3(256), 0, s, cp, ci, nblocks * k, k, dim,
                            static_cast<const int16_t *>(diag), d_idx, d_prob, d_cost);
         break;
     }
