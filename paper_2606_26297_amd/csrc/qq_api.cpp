@@ -1951,6 +1951,55 @@ qq_status qq_workspace_size(const qq_problem *pb, int p, int batch, int flags, s
     return QQ_OK;
 }
 
+// The workspace's result block to the caller's arrays.
+static hipError_t copy_results(int p, int batch, int flags, const char *ws, const Layout &L, double *energy_out,
+                               double *grad_out, hipMemcpyKind kind, hipStream_t stream)
+{
+    const double *d_out = reinterpret_cast<const double *>(ws + L.out);
+    const size_t row = (1 + 2 * (size_t)p) * sizeof(double), grow = 2 * (size_t)p * sizeof(double);
+    if (hipError_t e = hipMemcpy2DAsync(energy_out, sizeof(double), d_out, row, sizeof(double), batch, kind, stream);
+        e != hipSuccess || !(flags & QQ_GRAD))
+        return e;
+    return hipMemcpy2DAsync(grad_out, grow, d_out + 1, row, grow, batch, kind, stream);
+}
+
+// Whether the kernels may write the results to the caller's arrays themselves: memory of the problem's own
+// device (a copy also reaches a peer's or the host's, a kernel need not), apart from each other and from
+// the parameters, which a one-pass evaluation still reads while other sets' results are written.
+static bool writes_direct(const qq_problem *pb, int p, int batch, const double *params, int flags, const double *energy,
+                          const double *grad)
+{
+    const size_t ne = (size_t)batch, nx = ne * 2 * p, ng = (flags & QQ_GRAD) ? nx : 0;
+    auto apart = [](const double *a, size_t na, const double *b, size_t nb) {
+        const uintptr_t x = (uintptr_t)a, y = (uintptr_t)b;
+        return na == 0 || nb == 0 || x + na * sizeof(double) <= y || y + nb * sizeof(double) <= x;
+    };
+    auto own = [&](const double *q) {
+        hipPointerAttribute_t at;
+        if (hipPointerGetAttributes(&at, q) != hipSuccess) {
+            (void)hipGetLastError();
+            return false;
+        }
+        return at.type == hipMemoryTypeDevice && at.device == pb->device;
+    };
+    if (!apart(energy, ne, grad, ng)) return false;
+    if ((flags & QQ_PARAMS_ON_DEVICE) && (!apart(params, nx, energy, ne) || !apart(params, nx, grad, ng))) return false;
+    return own(energy) && (ng == 0 || own(grad));
+}
+
+// Evaluation into device arrays.
+static qq_status eval_to_device(qq_problem *pb, int p, int batch, const double *params, int flags, const Plan &plan,
+                                const Layout &L, char *ws, hipStream_t stream, double *energy_out, double *grad_out,
+                                bool capturing = false)
+{
+    const bool direct = writes_direct(pb, p, batch, params, flags, energy_out, grad_out);
+    const EvalOut out = direct ? EvalOut{energy_out, (flags & QQ_GRAD) ? grad_out : nullptr, 1, 2 * p}
+                               : ws_out(ws, L, p, flags);
+    if (qq_status st = eval_core(pb, p, batch, params, flags, plan, L, ws, stream, out, capturing); st != QQ_OK) return st;
+    if (!direct) QQ_HIP(copy_results(p, batch, flags, ws, L, energy_out, grad_out, hipMemcpyDeviceToDevice, stream));
+    return QQ_OK;
+}
+
 static qq_status evaluate_impl(qq_problem *pb, int p, int batch, const double *params, int flags, void *workspace,
                       size_t ws_bytes, void *stream_, double *energy_out, double *grad_out)
 {
@@ -1977,8 +2026,9 @@ static qq_status evaluate_impl(qq_problem *pb, int p, int batch, const double *p
     QQ_HIP(poison(ws, L.total, stream));
     const bool grad = flags & QQ_GRAD;
     if (flags & QQ_OUT_ON_DEVICE) {
-        const EvalOut out = {energy_out, grad ? grad_out : nullptr, 1, 2 * p};
-        if (qq_status st = eval_core(pb, p, batch, params, flags, plan, L, ws, stream, out); st != QQ_OK) return st;
+        if (qq_status st = eval_to_device(pb, p, batch, params, flags, plan, L, ws, stream, energy_out, grad_out);
+            st != QQ_OK)
+            return st;
         if (own.p) QQ_HIP(hipStreamSynchronize(stream));
         own.done();
         return QQ_OK;
@@ -2021,20 +2071,14 @@ static qq_status evaluate_static_impl(qq_problem *pb, int p, int batch, const do
     QQ_HIP(static_scratch(pb->device, &sp));
     char *ws = static_cast<char *>(sp);
     QQ_HIP(poison(ws, L.total, stream));
-    const bool grad = flags & QQ_GRAD, dev_out = flags & QQ_OUT_ON_DEVICE;
-    const EvalOut out = dev_out ? EvalOut{energy_out, grad ? grad_out : nullptr, 1, 2 * p} : ws_out(ws, L, p, flags);
     // no profiling events here (capturing = true): they are not part of the computation
-    if (qq_status st = eval_core(pb, p, batch, params, flags, plan, L, ws, stream, out, true); st != QQ_OK) return st;
-    if (!dev_out) {
-        const double *d_out = reinterpret_cast<const double *>(ws + L.out);
-        const size_t nout = 1 + 2 * (size_t)p;
-        QQ_HIP(hipMemcpy2DAsync(energy_out, sizeof(double), d_out, nout * sizeof(double), sizeof(double), batch,
-                                hipMemcpyDeviceToHost, stream));
-        if (grad)
-            QQ_HIP(hipMemcpy2DAsync(grad_out, 2 * p * sizeof(double), d_out + 1, nout * sizeof(double),
-                                    2 * p * sizeof(double), batch, hipMemcpyDeviceToHost, stream));
-    }
-    if (!(flags & QQ_OUT_ON_DEVICE)) QQ_HIP(hipStreamSynchronize(stream));
+    if (flags & QQ_OUT_ON_DEVICE)
+        return eval_to_device(pb, p, batch, params, flags, plan, L, ws, stream, energy_out, grad_out, true);
+    if (qq_status st = eval_core(pb, p, batch, params, flags, plan, L, ws, stream, ws_out(ws, L, p, flags), true);
+        st != QQ_OK)
+        return st;
+    QQ_HIP(copy_results(p, batch, flags, ws, L, energy_out, grad_out, hipMemcpyDeviceToHost, stream));
+    QQ_HIP(hipStreamSynchronize(stream));
     return QQ_OK;
 }
 
