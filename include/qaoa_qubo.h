@@ -208,9 +208,10 @@ qq_status qq_topk(qq_problem *prob, int p, const double *params, int flags, int 
  * three) drains a queue of (problem, parameter set, pass, tile chunk) items
  * from an atomic ticket, ordered by the fraction (j + 1) / L of its problem's
  * chain of L passes that pass j completes; a problem with n <= 12 is one item
- * per parameter set.  With QQ_C128 the items run the general complex128 pass
- * bodies of qq_evaluate (every problem by tile chunks; for n <= 12 one item of
- * one tile).  Items of a pass wait, bounded in time, for the previous
+ * per parameter set.  With QQ_C128 the items run the complex128 pass bodies of
+ * qq_evaluate in the same way.  A problem's results depend on its own inputs, the
+ * flags and opt->tiles_per_chunk alone, bit for bit: not on the other problems of
+ * the call nor on the grid.  Items of a pass wait, bounded in time, for the previous
  * pass on the same state; a wait longer than opt->wait_limit_ms sets a device
  * flag, the launch drains early and the call returns QQ_E_DEVICE.  The call
  * synchronises the stream before returning (it reads that flag).
@@ -224,7 +225,8 @@ qq_status qq_topk(qq_problem *prob, int p, const double *params, int flags, int 
  * QQ_E_NOMEM, QQ_E_DEVICE.
  */
 typedef struct {
-    int tiles_per_chunk;   /* tiles (4096 amplitudes) per work item of a multi-pass problem; 0: chosen from the batch */
+    int tiles_per_chunk;   /* tiles (4096 amplitudes) per work item of a multi-pass problem; 0: chosen from the
+                              batch, with the same results whatever the choice */
     int max_workgroups;    /* cap on the persistent grid; 0: every workgroup that fits on the device at once */
     double wait_limit_ms;  /* bound on one dependency wait; 0: 2000 ms */
 } qq_many_options;

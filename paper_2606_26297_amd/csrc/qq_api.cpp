@@ -1111,20 +1111,31 @@ uint64_t fnv1a(uint64_t h, int64_t v)
     return h;
 }
 
-// Tiles per item when the caller leaves them open.  An item of c tiles costs the launch a share of one
-// ticket, one wait and one completion (about 0.04 us of the whole chip per item in complex64, 0.07 in
-// complex128, from one-tile items: 512 problems 35.7 ms against 18.9, 128 problems 10.7 against 4.8),
-// so `items` one-tile items cost items * o / c; the longest chain of dependent passes runs its tiles one
-// after the other in at least L * c * u (u = 4 and 6.5 us per tile beside others).  The sum is least at
-// c = sqrt(items * o / (L * u)).  Measured (complex64, ms at 1 / 2 / 4 / 8 / 12 / 24 tiles, the rule's
-// choice): 512 problems of n <= 22 35.7 / 22.3 / 20.3 / 19.3 / 19.1 / 18.9 (19); 128 10.7 / 6.5 / 5.3 / 4.8 /
-// 5.0 / 6.5 (10); 96 of n <= 21 2.5 / 1.7 / 1.5 / 1.7 / 2.1 / 3.0 (6); 20 1.23 / 0.95 / 0.74 / 0.86 / 0.98 / 1.6
-// (3); 128 of n <= 14 0.14 / 0.18 / 0.28 (1).
-int many_tiles_per_chunk(double items, int longest, const qq_many_options *opt, bool c128)
+// Tiles per item when the caller leaves them open, for one launch (one diagonal type).  An item costs the launch a
+// share of one ticket, one wait, one set of coefficients and one completion (o = 0.0145 us of the whole chip in
+// complex64, 0.046 in complex128: one-tile items against the best, 512 and 128 problems), so `items` one-tile items
+// cost items * o / c at c tiles each; the longest chain of dependent passes runs its tiles one after the other in
+// at least L * c * u (u = 4 and 6.5 us per tile beside others).  The sum is least at c = sqrt(items * o / (L * u)).
+// Measured (complex64, ms at 1 / 2 / 4 / 8 / 12 / 24 tiles; the rule's choice and its time): 512 problems of
+// n <= 22 33.6 / 20.1 / 19.1 / 18.8 / 18.8 / 18.7 (12: 18.9); 128 10.5 / 6.4 / 6.0 / 5.9 / 6.0 / 7.5 (7: 6.0); 96 of
+// n <= 21 1.45 / 1.17 / 1.19 / 1.55 / 1.94 / 2.98 (3: 1.18); 20 2.15 / 1.37 / 1.35 / 1.72 / 2.17 / 3.08 (4: 1.33); 40 of
+// n <= 20 0.39 / 0.39 / 0.55 / 0.88 / 1.19 / 2.10 (2: 0.42); one of n = 22 1.63 / 1.62 / 1.33 / 1.43 / 1.93 / 3.16
+// (4: 1.33); 128 of n <= 14 0.13 / 0.17 / 0.28 (1: 0.13).
+int many_tiles_per_chunk(double items, int longest, bool c128)
 {
-    if (opt && opt->tiles_per_chunk > 0) return opt->tiles_per_chunk;
-    const double o = c128 ? 0.07 : 0.04, u = c128 ? 6.5 : 4.0;
+    const double o = c128 ? 0.046 : 0.0145, u = c128 ? 6.5 : 4.0;
     return (int)std::min(64.0, std::max(1.0, std::nearbyint(std::sqrt(items * o / (std::max(1, longest) * u)))));
+}
+
+// Tiles per partial sum (log2) when the caller leaves the item size open: the problem's own, whatever the batch, so
+// that its results do not depend on the batch.  At most 256 sums per pass up to n = 24, so that items as small as
+// a batch can want (one tile up to n = 20, four at n = 22) remain possible; a sum per tile costs an item about 3% of
+// its time.
+int many_unit_log2(uint64_t tiles)
+{
+    int k = 0;
+    while (k < 4 && (tiles >> (k + 9))) ++k;
+    return k;
 }
 
 qq_status plan_many(int count, qq_problem *const *pbs, const int *p, const int *batch, int flags,
@@ -1158,14 +1169,6 @@ qq_status plan_many(int count, qq_problem *const *pbs, const int *p, const int *
         M.out_off[i] = ooff;
         ooff += (size_t)batch[i] * (1 + 2 * p[i]);
     }
-    double one_tile_items = 0.0;
-    int longest = 1;
-    for (int i = 0; i < count; ++i) {
-        if (plans[i].sets.size() == 1) continue;
-        one_tile_items += (double)tiles_per_state(pbs[i]->n) * batch[i] * (double)plans[i].passes.size();
-        longest = std::max(longest, (int)plans[i].passes.size());
-    }
-    const uint64_t tpc = (uint64_t)many_tiles_per_chunk(one_tile_items, longest, opt, c128);
     size_t off = 0;
     M.params = off;
     off += align_up(poff * sizeof(double));
@@ -1177,6 +1180,14 @@ qq_status plan_many(int count, qq_problem *const *pbs, const int *p, const int *
         for (int i : order)
             if (pbs[i]->diag_type == dt) G.members.push_back(i);
         if (G.members.empty()) continue;
+        double one_tile_items = 0.0;
+        int longest = 1;
+        for (int i : G.members) {
+            if (plans[i].sets.size() == 1) continue;
+            one_tile_items += (double)tiles_per_state(pbs[i]->n) * batch[i] * (double)plans[i].passes.size();
+            longest = std::max(longest, (int)plans[i].passes.size());
+        }
+        const int open_tpc = many_tiles_per_chunk(one_tile_items, longest, c128);
         size_t state_off = 0;
         for (int i : G.members) {
             const qq_problem *pb = pbs[i];
@@ -1205,14 +1216,22 @@ qq_status plan_many(int count, qq_problem *const *pbs, const int *p, const int *
                 P.nslots = grad ? 1 + 2 * I.p : 1;
                 G.pass.push_back(P);
                 I.npasses = 1;
-                I.nchunks = 1;
+                I.nchunks = I.nunits = 1;
                 I.tpc = 1;
                 I.nslots = P.nslots;
                 for (int o = 0; o < I.nslots; ++o) G.slot_out.push_back((uint16_t)o);
                 G.bytes += (double)pb->dim * diag_bytes_of(pb->diag_type);
             } else {
                 I.shift = c128 ? 0.0 : pb->alpha;  // the complex64 pass bodies accumulate with C - alpha
-                I.tpc = (int)std::min(tpc, I.tiles);
+                if (opt && opt->tiles_per_chunk > 0) {
+                    I.tpc = (int)std::min<uint64_t>((uint64_t)opt->tiles_per_chunk, I.tiles);
+                    I.unit_log2 = __builtin_ctz((unsigned)I.tpc);
+                } else {  // the multiple of the unit next to the launch's choice
+                    I.unit_log2 = many_unit_log2(I.tiles);
+                    const int unit = 1 << I.unit_log2;
+                    I.tpc = (int)std::min<uint64_t>((uint64_t)std::max(1, (open_tpc + unit / 2) / unit) * unit, I.tiles);
+                }
+                I.nunits = (int)(I.tiles >> I.unit_log2);
                 I.nchunks = (int)((I.tiles + (uint64_t)I.tpc - 1) / (uint64_t)I.tpc);
                 I.npasses = (int)plan.passes.size();
                 int slot_base = 0;
@@ -1250,7 +1269,7 @@ qq_status plan_many(int count, qq_problem *const *pbs, const int *p, const int *
                     state_off += align_up(sb);
                 }
             }
-            G.partial_doubles += (size_t)I.nslots * I.B * I.nchunks;
+            G.partial_doubles += (size_t)I.nslots * I.B * I.nunits;
             G.inst.push_back(I);
         }
         G.state_bytes = state_off;

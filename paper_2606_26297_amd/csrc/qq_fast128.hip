@@ -29,7 +29,7 @@ fast_pass128(const p128::Args a)
             a.pre[(size_t)b * a.p + t] = make_double2(cb, sb);
         }
     }
-    const p128::Coef f = p128::coef<KIND, true>(a, b);
+    const p128::Coef f = p128::coef<KIND>(a, b);
     p128::pass_body<KIND, HIGH, FULL, PART>(a, lds, acc, t, b, g, f);
 
     if constexpr (NSLOT > 0) {

@@ -235,10 +235,11 @@ struct ManyInst {
     int n, p, B;
     int npasses, pass_off;  // passes in ManyPass[pass_off ..]
     int nchunks, tpc;
+    int nunits, unit_log2;  // partial sums per pass and slot, one per 2^unit_log2 tiles (which divide tpc and tiles)
     int nslots, slot_off;   // accumulator slots; their output indices in slot_out[slot_off ..]
     int state0;             // counter index of state 0
     uint64_t tiles, dim_mask;
-    uint64_t partial_off;   // doubles, laid out [slot][b][chunk]
+    uint64_t partial_off;   // doubles, laid out [slot][b][unit]
     double amp0, escale;
     double shift;           // centre of the cost for the accumulations of the pass bodies (multi-pass)
     const double *params;   // device [B][2p]

@@ -29,10 +29,10 @@
 // The complex128 launch keeps ordinary 16-byte accesses with a release and an
 // acquire per item (its amplitudes as two 8-byte atomics: 12.6 against 10.4 ms).
 //
-// Reductions.  Each item writes its workgroup's FP64 partial sums to a slot of
-// its own; the workgroup that completes the last item of a state sums the
-// partials in a fixed order (slots ascending, chunks ascending), so results are
-// reproducible run to run.
+// Reductions.  Each item writes its workgroup's FP64 partial sums, one per unit of its tiles; the workgroup that
+// completes the last item of a state sums the partials in a fixed order (finish_state).  The units are the
+// problem's own unless the caller sets the item size, so results are reproducible run to run and the same in
+// every batch.
 #include "qq_passes128.h"
 
 namespace qq {
@@ -215,29 +215,87 @@ __device__ void single_eval(const ManyInst &I, double *partial, float2 *lds, dou
 }
 
 // ---- multi-pass problems: one chunk of one pass ---------------------------------------------
+// Layer of an item's second mixer (its first one's is the pass's own layer k; the first pass's is 0).
+__device__ __forceinline__ int second_layer(int kind, int k)
+{
+    return kind == FK_TURN ? k + 1 : kind == FK_BTURN ? k - 1 : k;
+}
+
+// A wave's sum of one value per lane, in lane 63: rows of 16 by shifts inside the row, then across the rows
+// (DPP moves; the same sum over six dependent LDS permutes took 0.25 us per unit of a launch that waits on one
+// chain).
+template <int CTRL, int ROWS>
+__device__ __forceinline__ double dpp_add(double x)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, ROWS, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, ROWS, 0xf, true);
+    return x + __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double wave_total(double x)
+{
+    x = dpp_add<0x111, 0xf>(x);  // row_shr:1, 2, 4, 8: lane 15 of each row holds its row's sum
+    x = dpp_add<0x112, 0xf>(x);
+    x = dpp_add<0x114, 0xf>(x);
+    x = dpp_add<0x118, 0xf>(x);
+    x = dpp_add<0x142, 0xa>(x);     // row_bcast:15 into rows 1 and 3
+    return dpp_add<0x143, 0xc>(x);  // row_bcast:31 into rows 2 and 3
+}
+
+// The units of an item, in order: body(u0, acc) runs the unit's tiles from u0 on, and the workgroup's
+// fixed-order sums of acc are the unit's partial sums.  A unit is the problem's own (ManyInst::unit_log2), so that
+// a state's sums do not depend on how the launch splits it into items.  A body holds barriers, which
+// order one unit's reads of s_red before the next one's writes.
+template <typename Body>
+__device__ __forceinline__ void run_units(const ManyInst &I, const ManyPass &P, double *partial, double (*s_red)[4], int t,
+                                          int b, int chunk, Body body)
+{
+    const uint64_t t0 = (uint64_t)chunk * (uint64_t)I.tpc, t1 = min(I.tiles, t0 + (uint64_t)I.tpc);
+    for (uint64_t u0 = t0; u0 < t1; u0 += 1ull << I.unit_log2) {
+        double acc[3] = {0.0, 0.0, 0.0};
+        body(u0, acc);
+        if (P.nslots == 0) continue;
+        const int lane = t & 63, wave = t >> 6;
+#pragma unroll
+        for (int s = 0; s < 3; ++s) {
+            if (s >= P.nslots) break;
+            const double x = wave_total(acc[s]);
+            if (lane == 63) s_red[wave][s] = x;
+        }
+        __syncthreads();
+        if (t < P.nslots)
+            st_partial(partial + I.partial_off + ((size_t)(P.slot_base + t) * I.B + b) * I.nunits + (u0 >> I.unit_log2),
+                       (s_red[0][t] + s_red[1][t]) + (s_red[2][t] + s_red[3][t]));
+    }
+}
+
 template <int KIND, typename DT>
 __device__ __forceinline__ void run_geom(int geom, const FastArgs &a, float2 *lds, double (&acc)[3], int t, int b,
-                                         int g)
+                                         int g, const MixCoef *s_coef)
 {
+    MixCoef c1 = s_coef[0], c2{};
+    c1.formB = __builtin_amdgcn_readfirstlane(c1.formB);
+    if constexpr (kind_two<KIND>()) {
+        c2 = s_coef[1];
+        c2.formB = __builtin_amdgcn_readfirstlane(c2.formB);
+    }
+    const double g2pi = phase_gamma<KIND>(a.params + (size_t)b * 2 * a.p, a.k) * QQ_INV_TWO_PI;
     if (geom == 0) {
-        run_pass<KIND, false, true, DT, false, false, true, false>(a, lds, acc, t, b, g);
+        run_forms<KIND, false, true, DT, false, false, true, false>(a, lds, acc, t, b, g, c1, c2, g2pi);
     } else if constexpr (KIND != FK_FIRST) {  // the persistent plans take the qubit-0..11 set first
-        if (geom == 1) run_pass<KIND, true, true, DT, false, false, true, false>(a, lds, acc, t, b, g);
-        else run_pass<KIND, true, false, DT, false, false, true, false>(a, lds, acc, t, b, g);
+        if (geom == 1) run_forms<KIND, true, true, DT, false, false, true, false>(a, lds, acc, t, b, g, c1, c2, g2pi);
+        else run_forms<KIND, true, false, DT, false, false, true, false>(a, lds, acc, t, b, g, c1, c2, g2pi);
     }
 }
 
 template <typename DT>
 __device__ __forceinline__ void run_chunk(const ManyInst &I, const ManyPass &P, double *partial, float2 *lds,
-                                          double *s_red, int t, int b, int chunk)
+                                          double (*s_red)[4], MixCoef *s_coef, int t, int b, int chunk)
 {
     FastArgs a;
     a.B = I.B;
     a.G = 1;  // consecutive tiles
     a.p = I.p;
     a.k = P.k;
-    const uint64_t t0 = (uint64_t)chunk * (uint64_t)I.tpc;
-    a.tiles = min(I.tiles, t0 + (uint64_t)I.tpc);
     a.dim_mask = I.dim_mask;
     a.pos4 = P.pos4;
     a.pos8 = P.pos8;
@@ -265,43 +323,64 @@ __device__ __forceinline__ void run_chunk(const ManyInst &I, const ManyPass &P, 
     a.ctab = P.ctab;
     a.cthr = P.cthr;
     a.xtab = a.xthr = nullptr;  // no partitioned phases here
-    a.pre = nullptr;            // every item forms its own
-    a.ilv = 0;                  // separate psi and lambda arrays
-    double acc[3] = {0.0, 0.0, 0.0};
-    const int g = (int)t0;
-    switch (P.kind) {
-    case FK_FIRST: run_geom<FK_FIRST, DT>(P.geom, a, lds, acc, t, b, g); break;
-    case FK_MID: run_geom<FK_MID, DT>(P.geom, a, lds, acc, t, b, g); break;
-    case FK_TURN: run_geom<FK_TURN, DT>(P.geom, a, lds, acc, t, b, g); break;
-    case FK_LAST: run_geom<FK_LAST, DT>(P.geom, a, lds, acc, t, b, g); break;
-    case FK_LASTG: run_geom<FK_LASTG, DT>(P.geom, a, lds, acc, t, b, g); break;
-    case FK_BMID: run_geom<FK_BMID, DT>(P.geom, a, lds, acc, t, b, g); break;
-    case FK_BTURN: run_geom<FK_BTURN, DT>(P.geom, a, lds, acc, t, b, g); break;
-    default: run_geom<FK_BLAST, DT>(P.geom, a, lds, acc, t, b, g); break;
+    a.pre = nullptr;
+    a.ilv = 0;  // separate psi and lambda arrays
+    // the item's coefficients, formed by one thread each
+    if (t < 2) {
+        const int k = P.kind == FK_FIRST ? 0 : t == 0 ? P.k : second_layer(P.kind, P.k);
+        const bool inverse = P.kind >= FK_BMID || (t == 1 && P.kind == FK_LASTG);
+        s_coef[t] = mix_coef(I.params[((size_t)b * I.p + k) * 2 + 1], inverse, P.nact);
     }
-    // partial sums: slot (P.slot_base + s), state b, chunk
-#pragma unroll
-    for (int s = 0; s < 3; ++s) {
-        if (s >= P.nslots) break;
-        const double v = wg_sum(acc[s], s_red, t);
-        if (t == 0) st_partial(partial + I.partial_off + ((size_t)(P.slot_base + s) * I.B + b) * I.nchunks + chunk, v);
-    }
+    __syncthreads();
+    run_units(I, P, partial, s_red, t, b, chunk, [&](uint64_t u0, double (&acc)[3]) __attribute__((always_inline)) {
+        a.tiles = u0 + (1ull << I.unit_log2);
+        const int g = (int)u0, ti = fresh_index(t);
+        switch (P.kind) {
+        case FK_FIRST: run_geom<FK_FIRST, DT>(P.geom, a, lds, acc, ti, b, g, s_coef); break;
+        case FK_MID: run_geom<FK_MID, DT>(P.geom, a, lds, acc, ti, b, g, s_coef); break;
+        case FK_TURN: run_geom<FK_TURN, DT>(P.geom, a, lds, acc, ti, b, g, s_coef); break;
+        case FK_LAST: run_geom<FK_LAST, DT>(P.geom, a, lds, acc, ti, b, g, s_coef); break;
+        case FK_LASTG: run_geom<FK_LASTG, DT>(P.geom, a, lds, acc, ti, b, g, s_coef); break;
+        case FK_BMID: run_geom<FK_BMID, DT>(P.geom, a, lds, acc, ti, b, g, s_coef); break;
+        case FK_BTURN: run_geom<FK_BTURN, DT>(P.geom, a, lds, acc, ti, b, g, s_coef); break;
+        default: run_geom<FK_BLAST, DT>(P.geom, a, lds, acc, ti, b, g, s_coef); break;
+        }
+    });
 }
 
-// Final results of state b: fixed-order sums of its partials.
-__device__ void finish_state(const ManyArgs &A, const ManyInst &I, int b, int t)
+// Final results of state b: fixed-order sums of its partials.  16 lanes take a slot's units side by side, the
+// workgroup 16 slots at once; one thread per output then adds the slots mapped to it.  Bound by the latency of
+// reads beyond the L2, four in flight per lane; it stands at the end of every chain (one thread per output and
+// one read at a time: one problem of n = 22, p = 6, whole call 2.45 ms against 1.33).
+__device__ void finish_state(const ManyArgs &A, const ManyInst &I, double *lds, int b, int t)
 {
+    double *tot = lds;                                     // [nslots]
+    int *out = reinterpret_cast<int *>(lds + kMaxSlots);  // [nslots]
+    const int lane = t & 15;
+    for (int s = t >> 4; s < I.nslots; s += kThreads / 16) {
+        const double *src = A.partial + I.partial_off + ((size_t)s * I.B + b) * I.nunits;
+        double x = 0.0;
+        for (int c = lane; c < I.nunits; c += 64) {
+            double v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = c + 16 * u < I.nunits ? ld_partial(src + c + 16 * u) : 0.0;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) x += v[u];
+        }
+#pragma unroll
+        for (int d = 8; d >= 1; d >>= 1) x += __shfl_xor(x, d, 64);
+        if (lane == 0) {
+            tot[s] = x;
+            out[s] = A.slot_out[I.slot_off + s];
+        }
+    }
+    __syncthreads();
     const int nout = A.grad ? 1 + 2 * I.p : 1;
     for (int o = t; o < nout; o += kThreads) {
-        double tot = 0.0;
-        for (int s = 0; s < I.nslots; ++s) {
-            if ((int)A.slot_out[I.slot_off + s] != o) continue;
-            const double *src = A.partial + I.partial_off + ((size_t)s * I.B + b) * I.nchunks;
-            double x = 0.0;
-            for (int c = 0; c < I.nchunks; ++c) x += ld_partial(src + c);
-            tot += x;
-        }
-        const double v = o == 0 ? tot * I.escale + I.shift : tot * (2.0 * I.escale);
+        double sum = 0.0;
+        for (int s = 0; s < I.nslots; ++s)
+            if (out[s] == o) sum += tot[s];
+        const double v = o == 0 ? sum * I.escale + I.shift : sum * (2.0 * I.escale);
         if (I.energy_out) {
             if (o == 0) I.energy_out[b] = v;
             else I.grad_out[(size_t)b * 2 * I.p + (o - 1)] = v;
@@ -309,6 +388,7 @@ __device__ void finish_state(const ManyArgs &A, const ManyInst &I, int b, int t)
             I.out_ws[(size_t)b * (1 + 2 * I.p) + o] = v;
         }
     }
+    __syncthreads();  // the next item's body writes lds
 }
 
 // FENCED: an agent-scope release and acquire per item (bodies with ordinary state accesses).
@@ -317,7 +397,7 @@ __device__ void finish_state(const ManyArgs &A, const ManyInst &I, int b, int t)
 // the item, and let the workgroup that completes a state's last item finish that state.  The item
 // bodies are lambdas marked always_inline: called out of line, they spill registers across the call.
 template <bool FENCED, typename Run>
-__device__ __forceinline__ void drain_queue(const ManyArgs &A, uint32_t *s_msg, int t, Run run)
+__device__ __forceinline__ void drain_queue(const ManyArgs &A, uint32_t *s_msg, double *lds, int t, Run run)
 {
     uint32_t *head = A.ctl, *err = A.ctl + kCtlStride, *cnt = A.ctl + 2 * kCtlStride;
     int seg0 = 0;  // a segment at or before the next ticket's (tickets only grow)
@@ -396,7 +476,7 @@ __device__ __forceinline__ void drain_queue(const ManyArgs &A, uint32_t *s_msg, 
         __syncthreads();
         const uint32_t last = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_msg[0]);
         __syncthreads();
-        if (last) finish_state(A, I, b, t);
+        if (last) finish_state(A, I, lds, b, t);
     }
 }
 
@@ -404,11 +484,11 @@ template <typename DT>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3))) many_kernel(const ManyArgs A)
 {
     __shared__ float2 lds[kLdsSlots];
-    __shared__ double s_red[kThreads / 64];
+    __shared__ double s_red[kThreads / 64][4];
     __shared__ uint32_t s_msg[2];
     __shared__ MixCoef s_coef[2 * QQ_MAX_P];
     const int t = threadIdx.x;
-    drain_queue<false>(A, s_msg, t, [&](const ManyInst &I, int pass, int b, int chunk) __attribute__((always_inline)) {
+    drain_queue<false>(A, s_msg, reinterpret_cast<double *>(lds), t, [&](const ManyInst &I, int pass, int b, int chunk) __attribute__((always_inline)) {
         const ManyPass &P = A.pass[I.pass_off + pass];
         // The thread index, opaque per item: keeps each body's index arithmetic
         // inside its own branch instead of hoisted out of the item loop (where
@@ -416,10 +496,10 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3
         int ti = t;
         asm volatile("" : "+v"(ti));
         if (P.kind == FK_SINGLE) {
-            if (A.grad) single_eval<DT, true>(I, A.partial, lds, s_red, s_coef, ti, b);
-            else single_eval<DT, false>(I, A.partial, lds, s_red, s_coef, ti, b);
+            if (A.grad) single_eval<DT, true>(I, A.partial, lds, s_red[0], s_coef, ti, b);
+            else single_eval<DT, false>(I, A.partial, lds, s_red[0], s_coef, ti, b);
         } else {
-            run_chunk<DT>(I, P, A.partial, lds, s_red, ti, b, chunk);
+            run_chunk<DT>(I, P, A.partial, lds, s_red, s_coef, ti, b, chunk);
         }
     });
 }
@@ -427,9 +507,9 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(3
 // ---- complex128 states -------------------------------------------------------------------------
 template <int KIND>
 __device__ __forceinline__ void run_geom128(int geom, const p128::Args &a, double2 *lds, double (&acc)[3], int t, int b,
-                                            int g)
+                                            int g, const double2 *s_cs)
 {
-    const p128::Coef f = p128::coef<KIND, false>(a, b);
+    const p128::Coef f = p128::coef_of<KIND>(s_cs[0], s_cs[1], a.params + (size_t)b * 2 * a.p, a.k);
     // one-state kinds transpose in two rounds of 8-byte words (registers bound this kernel, not LDS)
     using W = typename std::conditional<kind_states<KIND>() == 2, double2, double>::type;
     W *l = reinterpret_cast<W *>(lds);
@@ -442,15 +522,13 @@ __device__ __forceinline__ void run_geom128(int geom, const p128::Args &a, doubl
 }
 
 __device__ __forceinline__ void run_chunk128(const ManyInst &I, const ManyPass &P, double *partial, double2 *lds,
-                                             double *s_red, int t, int b, int chunk)
+                                             double (*s_red)[4], double2 *s_cs, int t, int b, int chunk)
 {
     p128::Args a;
-    const uint64_t t0 = (uint64_t)chunk * (uint64_t)I.tpc;
     a.B = I.B;
     a.G = 1;  // consecutive tiles
     a.p = I.p;
     a.k = P.k;
-    a.tiles = min(I.tiles, t0 + (uint64_t)I.tpc);
     a.pos4 = P.pos4;
     a.pos8 = P.pos8;
     a.w1 = P.w1;
@@ -470,25 +548,28 @@ __device__ __forceinline__ void run_chunk128(const ManyInst &I, const ManyPass &
     a.ctab = P.ctab;
     a.cthr = P.cthr;
     a.ltab = a.lthr = a.xtab = a.xthr = nullptr;  // no partitioned phases here
-    a.pre = nullptr;                              // every item forms its own
-    double acc[3] = {0.0, 0.0, 0.0};
-    const int g = (int)t0;
-    switch (P.kind) {
-    case FK_FIRST: run_geom128<FK_FIRST>(P.geom, a, lds, acc, t, b, g); break;
-    case FK_MID: run_geom128<FK_MID>(P.geom, a, lds, acc, t, b, g); break;
-    case FK_TURN: run_geom128<FK_TURN>(P.geom, a, lds, acc, t, b, g); break;
-    case FK_LAST: run_geom128<FK_LAST>(P.geom, a, lds, acc, t, b, g); break;
-    case FK_LASTG: run_geom128<FK_LASTG>(P.geom, a, lds, acc, t, b, g); break;
-    case FK_BMID: run_geom128<FK_BMID>(P.geom, a, lds, acc, t, b, g); break;
-    case FK_BTURN: run_geom128<FK_BTURN>(P.geom, a, lds, acc, t, b, g); break;
-    default: run_geom128<FK_BLAST>(P.geom, a, lds, acc, t, b, g); break;
+    a.pre = nullptr;
+    if (t < 2) {
+        const int k = P.kind == FK_FIRST ? 0 : t == 0 ? P.k : second_layer(P.kind, P.k);
+        double sb, cb;
+        sincos(I.params[((size_t)b * I.p + k) * 2 + 1], &sb, &cb);
+        s_cs[t] = make_double2(cb, sb);
     }
-#pragma unroll
-    for (int s = 0; s < 3; ++s) {
-        if (s >= P.nslots) break;
-        const double v = wg_sum(acc[s], s_red, t);
-        if (t == 0) st_partial(partial + I.partial_off + ((size_t)(P.slot_base + s) * I.B + b) * I.nchunks + chunk, v);
-    }
+    __syncthreads();
+    run_units(I, P, partial, s_red, t, b, chunk, [&](uint64_t u0, double (&acc)[3]) __attribute__((always_inline)) {
+        a.tiles = u0 + (1ull << I.unit_log2);
+        const int g = (int)u0, ti = fresh_index(t);
+        switch (P.kind) {
+        case FK_FIRST: run_geom128<FK_FIRST>(P.geom, a, lds, acc, ti, b, g, s_cs); break;
+        case FK_MID: run_geom128<FK_MID>(P.geom, a, lds, acc, ti, b, g, s_cs); break;
+        case FK_TURN: run_geom128<FK_TURN>(P.geom, a, lds, acc, ti, b, g, s_cs); break;
+        case FK_LAST: run_geom128<FK_LAST>(P.geom, a, lds, acc, ti, b, g, s_cs); break;
+        case FK_LASTG: run_geom128<FK_LASTG>(P.geom, a, lds, acc, ti, b, g, s_cs); break;
+        case FK_BMID: run_geom128<FK_BMID>(P.geom, a, lds, acc, ti, b, g, s_cs); break;
+        case FK_BTURN: run_geom128<FK_BTURN>(P.geom, a, lds, acc, ti, b, g, s_cs); break;
+        default: run_geom128<FK_BLAST>(P.geom, a, lds, acc, ti, b, g, s_cs); break;
+        }
+    });
 }
 
 // The specialised complex128 bodies behind the same queue, two workgroups per compute unit (the
@@ -497,11 +578,11 @@ template <typename DT>
 __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2))) many128_kernel(const ManyArgs A)
 {
     __shared__ double2 lds[kLdsSlots];
-    __shared__ double s_red[kThreads / 64];
+    __shared__ double s_red[kThreads / 64][4];
     __shared__ uint32_t s_msg[2];
     __shared__ double2 s_cs[QQ_MAX_P];
     const int t = threadIdx.x;
-    drain_queue<true>(A, s_msg, t, [&](const ManyInst &I, int pass, int b, int chunk) __attribute__((always_inline)) {
+    drain_queue<true>(A, s_msg, reinterpret_cast<double *>(lds), t, [&](const ManyInst &I, int pass, int b, int chunk) __attribute__((always_inline)) {
         const ManyPass &P = A.pass[I.pass_off + pass];
         int ti = t;
         asm volatile("" : "+v"(ti));  // each body forms its indexes itself
@@ -509,10 +590,10 @@ __global__ void __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2
             const p128::Single e = {I.n, I.p, I.amp0, I.params + (size_t)b * 2 * I.p, I.diag};
             double *out = A.partial + I.partial_off + b;  // slot o at out[o * B]
             auto put = [&](int o, double v) __attribute__((always_inline)) { st_partial(out + (size_t)o * I.B, v); };
-            if (A.grad) p128::single_eval<2, DT>(e, lds, s_red, s_cs, ti, nullptr, put);
-            else p128::single_eval<1, DT>(e, lds, s_red, s_cs, ti, nullptr, put);
+            if (A.grad) p128::single_eval<2, DT>(e, lds, s_red[0], s_cs, ti, nullptr, put);
+            else p128::single_eval<1, DT>(e, lds, s_red[0], s_cs, ti, nullptr, put);
         } else {
-            run_chunk128(I, P, A.partial, lds, s_red, ti, b, chunk);
+            run_chunk128(I, P, A.partial, lds, s_red, s_cs, ti, b, chunk);
         }
     });
 }

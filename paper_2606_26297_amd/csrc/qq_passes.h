@@ -975,21 +975,53 @@ __device__ __forceinline__ void pass_body(const FastArgs &a, float2 *lds, double
     }
 }
 
-// Layer constants of one pass for parameter set x, then one uniform dispatch on
-// the forms of the (up to two) mixer coefficients, so the butterfly code of each
-// path has no form branch.  Tiles g, g + a.G, ... below a.tiles.
-template <int KIND, bool HIGH, bool FULL, typename DT, bool PART = false, bool WIDE = false, bool CT = false,
-          bool PR = true>
+// Whether a kind has a second mixer, and the layer of its phase in terms of its own layer k.
+template <int KIND>
+constexpr bool kind_two()
+{
+    return KIND == FK_TURN || KIND == FK_LASTG || KIND == FK_BTURN;
+}
+template <int KIND>
+__device__ __forceinline__ double phase_gamma(const double *x, int k)
+{
+    if constexpr (KIND == FK_FIRST) return x[0];
+    else if constexpr (KIND == FK_TURN) return x[2 * (k + 1)];
+    else if constexpr (KIND == FK_BTURN) return x[2 * k];
+    else return 0.0;
+}
+
+// Tiles g, g + a.G, ... below a.tiles: one uniform dispatch on the forms of the (up to two) mixer
+// coefficients, so the butterfly code of each path has no form branch.
+template <int KIND, bool HIGH, bool FULL, typename DT, bool PART, bool WIDE, bool CT, bool PR>
+__device__ __forceinline__ void run_forms(const FastArgs &a, float2 *lds, double (&acc)[3], int t, int b, int g,
+                                          const MixCoef &c1, const MixCoef &c2, double g2pi)
+{
+    constexpr bool TWO = kind_two<KIND>();
+    if constexpr (!FULL) {
+        // general butterflies: one body serves both forms
+        pass_body<KIND, HIGH, FULL, DT, PART, WIDE, false, false, CT, PR>(a, lds, acc, t, b, g, c1, c2, g2pi);
+        return;
+    }
+    const int sel = (c1.formB ? 1 : 0) | (TWO && c2.formB ? 2 : 0);
+    if (sel == 0) pass_body<KIND, HIGH, FULL, DT, PART, WIDE, false, false, CT, PR>(a, lds, acc, t, b, g, c1, c2, g2pi);
+    else if (sel == 1) pass_body<KIND, HIGH, FULL, DT, PART, WIDE, true, false, CT, PR>(a, lds, acc, t, b, g, c1, c2, g2pi);
+    else if constexpr (TWO) {
+        if (sel == 2) pass_body<KIND, HIGH, FULL, DT, PART, WIDE, false, true, CT, PR>(a, lds, acc, t, b, g, c1, c2, g2pi);
+        else pass_body<KIND, HIGH, FULL, DT, PART, WIDE, true, true, CT, PR>(a, lds, acc, t, b, g, c1, c2, g2pi);
+    }
+}
+
+// One pass of a per-pass kernel: its layer constants for parameter set b, then its tiles.
+template <int KIND, bool HIGH, bool FULL, typename DT, bool PART, bool WIDE, bool CT>
 __device__ __forceinline__ void run_pass(const FastArgs &a, float2 *lds, double (&acc)[3], int t, int b, int g)
 {
     const double *x = a.params + (size_t)b * 2 * a.p;
     MixCoef c1{}, c2{};
-    double gam = 0.0;
-    // the coefficients of layer k (wave-uniform): from the first pass's table in the per-pass kernels (a sine,
-    // a cosine, a division and a root in FP64 per layer and workgroup are 1 to 2 us of a 10 us launch at
-    // n = 16), formed here in the persistent launch and in the first pass
+    // the coefficients of layer k (wave-uniform), from the first pass's table (a sine, a cosine, a division and
+    // a root in FP64 per layer and workgroup are 1 to 2 us of a 10 us launch at n = 16); the first pass itself
+    // forms its own
     auto mix = [&](int k, bool inverse) {
-        if constexpr (PR && KIND != FK_FIRST) {
+        if constexpr (KIND != FK_FIRST) {
             const auto *q = (const MixPre __attribute__((address_space(4))) *)(a.pre + (size_t)b * a.p + k);
             MixPre r;
             r.m = q->m;
@@ -1005,13 +1037,11 @@ __device__ __forceinline__ void run_pass(const FastArgs &a, float2 *lds, double 
         }
     };
     if constexpr (KIND == FK_FIRST) {
-        gam = x[0];
         c1 = mix(0, false);
     } else if constexpr (KIND == FK_MID || KIND == FK_LAST) {
         c1 = mix(a.k, false);
     } else if constexpr (KIND == FK_TURN) {
         c1 = mix(a.k, false);
-        gam = x[2 * (a.k + 1)];
         c2 = mix(a.k + 1, false);
     } else if constexpr (KIND == FK_LASTG) {
         c1 = mix(a.k, false);
@@ -1020,23 +1050,10 @@ __device__ __forceinline__ void run_pass(const FastArgs &a, float2 *lds, double 
         c1 = mix(a.k, true);
     } else if constexpr (KIND == FK_BTURN) {
         c1 = mix(a.k, true);
-        gam = x[2 * a.k];
         c2 = mix(a.k - 1, true);
     }
-    const double g2pi = gam * QQ_INV_TWO_PI;
-    constexpr bool TWO = KIND == FK_TURN || KIND == FK_LASTG || KIND == FK_BTURN;
-    if constexpr (!FULL) {
-        // general butterflies: one body serves both forms
-        pass_body<KIND, HIGH, FULL, DT, PART, WIDE, false, false, CT, PR>(a, lds, acc, t, b, g, c1, c2, g2pi);
-        return;
-    }
-    const int sel = (c1.formB ? 1 : 0) | (TWO && c2.formB ? 2 : 0);
-    if (sel == 0) pass_body<KIND, HIGH, FULL, DT, PART, WIDE, false, false, CT, PR>(a, lds, acc, t, b, g, c1, c2, g2pi);
-    else if (sel == 1) pass_body<KIND, HIGH, FULL, DT, PART, WIDE, true, false, CT, PR>(a, lds, acc, t, b, g, c1, c2, g2pi);
-    else if constexpr (TWO) {
-        if (sel == 2) pass_body<KIND, HIGH, FULL, DT, PART, WIDE, false, true, CT, PR>(a, lds, acc, t, b, g, c1, c2, g2pi);
-        else pass_body<KIND, HIGH, FULL, DT, PART, WIDE, true, true, CT, PR>(a, lds, acc, t, b, g, c1, c2, g2pi);
-    }
+    const double g2pi = phase_gamma<KIND>(x, a.k) * QQ_INV_TWO_PI;
+    run_forms<KIND, HIGH, FULL, DT, PART, WIDE, CT, true>(a, lds, acc, t, b, g, c1, c2, g2pi);
 }
 
 // Fixed-order workgroup sum of one FP64 value per thread (all threads get the result).

@@ -236,43 +236,47 @@ struct Coef {
     double c1, s1, c2, s2, gam;
 };
 
-// TABLE: from the first pass's (cos, sin) per layer (the first pass itself forms its own).
-template <int KIND, bool TABLE>
+// From the (cos, sin) of the kind's own layer k and, where it has a second mixer of another layer, of that one.
+template <int KIND>
+__device__ __forceinline__ Coef coef_of(double2 first, double2 second, const double *x, int k)
+{
+    Coef f{};
+    f.c1 = first.x;
+    f.s1 = KIND >= FK_BMID ? -first.y : first.y;
+    f.gam = passes::phase_gamma<KIND>(x, k);
+    if constexpr (KIND == FK_TURN) {
+        f.c2 = second.x;
+        f.s2 = second.y;
+    } else if constexpr (KIND == FK_LASTG) {
+        f.c2 = first.x;
+        f.s2 = -first.y;
+    } else if constexpr (KIND == FK_BTURN) {
+        f.c2 = second.x;
+        f.s2 = -second.y;
+    }
+    return f;
+}
+// In a per-pass kernel: from the first pass's (cos, sin) per layer (the first pass itself forms its own).
+template <int KIND>
 __device__ __forceinline__ Coef coef(const Args &a, int b)
 {
     const double *x = a.params + (size_t)b * 2 * a.p;
     const int k = a.k;
-    auto cs = [&](int layer, double &c, double &s) {
-        if constexpr (TABLE && KIND != FK_FIRST) {
+    auto cs = [&](int layer) {
+        if constexpr (KIND != FK_FIRST) {
             const auto *q = (const double __attribute__((address_space(4))) *)(a.pre + (size_t)b * a.p + layer);
-            c = q[0];
-            s = q[1];
+            return make_double2(q[0], q[1]);
         } else {
+            double s, c;
             sincos(x[2 * layer + 1], &s, &c);
+            return make_double2(c, s);
         }
     };
-    Coef f{};
-    if constexpr (KIND == FK_FIRST) {
-        f.gam = x[0];
-        cs(0, f.c1, f.s1);
-    } else {
-        cs(k, f.c1, f.s1);
-        if constexpr (KIND == FK_TURN) {
-            f.gam = x[2 * (k + 1)];
-            cs(k + 1, f.c2, f.s2);
-        } else if constexpr (KIND == FK_LASTG) {
-            f.c2 = f.c1;
-            f.s2 = -f.s1;
-        } else if constexpr (KIND == FK_BMID || KIND == FK_BLAST) {
-            f.s1 = -f.s1;
-        } else if constexpr (KIND == FK_BTURN) {
-            f.s1 = -f.s1;
-            f.gam = x[2 * k];
-            cs(k - 1, f.c2, f.s2);
-            f.s2 = -f.s2;
-        }
-    }
-    return f;
+    const double2 first = cs(KIND == FK_FIRST ? 0 : k);
+    double2 second = make_double2(0.0, 0.0);
+    if constexpr (KIND == FK_TURN) second = cs(k + 1);
+    if constexpr (KIND == FK_BTURN) second = cs(k - 1);
+    return coef_of<KIND>(first, second, x, k);
 }
 
 // The tile loop of one pass kind (the kinds' operations are listed in qq_passes.h).
