@@ -2402,9 +2402,11 @@ qq_status qq_topk(qq_problem *pb, int p, const double *params, int flags, int k,
     Layout L;
     if (qq_status st = state_into(pb, p, params, flags, stream, own, L); st != QQ_OK) return st;
     const void *psi = static_cast<char *>(own.p) + L.psi;
-    // 512 workgroups: every wave pays for the insertions of its first amplitudes, and stage 2 reads k candidates
-    // per workgroup (n = 24, the whole call: 128 workgroups 550 us, 256 513, 512 499, 1024 526)
-    const int nblocks = (int)std::min<uint64_t>(512, (pb->dim + 255) / 256);
+    // 512 workgroups up to n = 26, 1024 beyond: every wave pays for the insertions of its first amplitudes and
+    // stage 2 reads k candidates per workgroup, while 512 workgroups keep too few reads in flight for the largest
+    // states.  Both stages, us at 256 / 512 / 1024 workgroups: n = 20, k = 10 59 / 63 / 76; n = 24 140 / 121 / 142;
+    // n = 26 274 / 209 / 206, k = 16 318 / 250 / 271; n = 28, k = 1 790 / 508 / 461, k = 16 867 / 571 / 559
+    const int nblocks = (int)std::min<uint64_t>(pb->dim > (1ull << 26) ? 1024 : 512, (pb->dim + 255) / 256);
     DevBuf scratch;
     const size_t sb = (size_t)nblocks * k * 16 + (size_t)k * 24 + 256;
     if (scratch.get(pb->device, sb) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc failed");
