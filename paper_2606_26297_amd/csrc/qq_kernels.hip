@@ -64,7 +64,17 @@ __global__ void __launch_bounds__(256) finalize_kernel(const FinalizeArgs a)
     for (int s = 0; s < a.nslots; ++s) {
         if (a.slot_out[s] != o) continue;
         const double *src = a.partial + ((size_t)s * a.B + b) * a.G;
-        for (int gg = t; gg < a.G; gg += 256) x += src[gg];
+        int gg = t;
+        // eight reads in flight, added in order (one at a time: 84 us at n = 28, one state, 16384 sums per slot,
+        // against 26)
+        for (; gg + 7 * 256 < a.G; gg += 8 * 256) {
+            double v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = src[gg + 256 * u];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x += v[u];
+        }
+        for (; gg < a.G; gg += 256) x += src[gg];
     }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) x += __shfl_xor(x, d, 64);
@@ -93,7 +103,7 @@ __device__ __forceinline__ double lane_of(double x, int l)
                             __builtin_amdgcn_readlane(__double2loint(x), l));
 }
 
-template <bool INT, typename DT>
+template <bool INT, bool LANES, typename DT>
 __global__ void __launch_bounds__(256) cost_diag_kernel(int n, uint64_t dim, const double *ell, const int32_t *ell_i,
                                                          int npairs, const int32_t *pij, const double *pb,
                                                          const int32_t *pbi, double c0, int32_t c0_i, DT *out)
@@ -121,22 +131,34 @@ __global__ void __launch_bounds__(256) cost_diag_kernel(int n, uint64_t dim, con
     if (threadIdx.x == 0)
         for (int r = n - 1; r >= 0; --r) s_rows[r] = min(s_rows[r], s_rows[r + 1]);
     __syncthreads();
-    // lane r holds the first pair of row r and the linear term r, lane k the pair k of the chunk of 64 pairs
-    // in hand; the loops read them with readlane, so no memory latency sits in the chain of additions
-    // (scalar loads per term took a dense n = 18 diagonal 31 us, whatever its size)
+    // lane r holds the first pair of row r; read with readlane (no memory latency in the row loop)
     const int lane = threadIdx.x & 63;
     const int vrows = s_rows[min(lane, n)];
-    const Acc vell = lane < n ? (INT ? (Acc)ell_i[lane] : (Acc)ell[lane]) : (Acc)0;
+    // The terms.  LANES: lane r holds the linear term r, lane k the pair k of the chunk of 64 pairs in hand, read
+    // with readlane, so no memory latency sits in the chain of additions.  Otherwise scalar loads, which cost
+    // fewer instructions and hide behind the other waves where there are enough of them.
+    const Acc vell = LANES && lane < n ? (INT ? (Acc)ell_i[lane] : (Acc)ell[lane]) : (Acc)0;
     int chunk = -1, cj = 0;
     Acc cw = 0;
-    auto pair_chunk = [&](int k) {
-        if ((k >> 6) == chunk) return;
-        chunk = k >> 6;
-        const int kk = min(64 * chunk + lane, npairs - 1);
-        cj = pij[2 * kk + 1];
-        cw = INT ? (Acc)pbi[kk] : (Acc)pb[kk];
+    auto linear = [&](int i) -> Acc {
+        if constexpr (LANES) return lane_of(vell, i);
+        else return INT ? (Acc)ell_i[i] : (Acc)ell[i];
     };
-    if (npairs > 0) pair_chunk(0);
+    auto pair = [&](int k, int &j) -> Acc {
+        if constexpr (LANES) {
+            if ((k >> 6) != chunk) {
+                chunk = k >> 6;
+                const int kk = min(64 * chunk + lane, npairs - 1);
+                cj = pij[2 * kk + 1];
+                cw = INT ? (Acc)pbi[kk] : (Acc)pb[kk];
+            }
+            j = __builtin_amdgcn_readlane(cj, k & 63);
+            return lane_of(cw, k & 63);
+        } else {
+            j = pij[2 * k + 1];
+            return INT ? (Acc)pbi[k] : (Acc)pb[k];
+        }
+    };
 
     const uint32_t lo = 4u * (uint32_t)lane;
     const uint64_t nw = (uint64_t)gridDim.x * (blockDim.x >> 6);
@@ -148,7 +170,7 @@ __global__ void __launch_bounds__(256) cost_diag_kernel(int n, uint64_t dim, con
         for (int u = 0; u < 4; ++u) acc[u] = INT ? (Acc)c0_i : (Acc)c0;
         for (int i = 0; i < n; ++i) {
             const int iu = __builtin_amdgcn_readfirstlane(i);
-            const Acc l = lane_of(vell, iu);
+            const Acc l = linear(iu);
             if (iu < kLow) {
 #pragma unroll
                 for (int u = 0; u < 4; ++u) acc[u] = (((lo + u) >> iu) & 1u) ? acc[u] + l : acc[u];
@@ -165,24 +187,20 @@ __global__ void __launch_bounds__(256) cost_diag_kernel(int n, uint64_t dim, con
             const int k1 = __builtin_amdgcn_readlane(vrows, ru + 1);
             if (ru >= kLow) {
                 // both bits are wave-uniform: the coefficient or the neutral element, added everywhere
-
                 for (int k = k0; k < k1; ++k) {
                     const int ku = __builtin_amdgcn_readfirstlane(k);
-                    pair_chunk(ku);
-                    const int j = __builtin_amdgcn_readlane(cj, ku & 63);
-                    const Acc wv = lane_of(cw, ku & 63);
+                    int j;
+                    const Acc wv = pair(ku, j);
                     const Acc wu = ((zb >> j) & 1ull) ? wv : neutral;
 #pragma unroll
                     for (int u = 0; u < 4; ++u) acc[u] += wu;
                 }
             } else {
                 // bit r varies inside the wave; bit j does below 8, is wave-uniform from 8 on
-
                 for (int k = k0; k < k1; ++k) {
                     const int ku = __builtin_amdgcn_readfirstlane(k);
-                    pair_chunk(ku);
-                    const int j = __builtin_amdgcn_readlane(cj, ku & 63);
-                    const Acc wv = lane_of(cw, ku & 63);
+                    int j;
+                    const Acc wv = pair(ku, j);
                     const uint32_t hj = (uint32_t)((zb >> j) & 1ull);
 #pragma unroll
                     for (int u = 0; u < 4; ++u) {
@@ -598,9 +616,17 @@ hipError_t launch_cost_diag(int n, int diag_type, const double *d_ell, const int
 {
     // 256 indices per wave, 1024 per workgroup of four waves
     const dim3 grid(grid_for((dim + 3) / 4, 65536)), block(256);
-#define QQ_COST_DIAG(INT, DT)                                                                                     \
-    hipLaunchKernelGGL((cost_diag_kernel<INT, DT>), grid, block, 0, s, n, dim, d_ell, d_ell_i, npairs, d_pair_ij,   \
-                       d_pair_b, d_pair_bi, c0, c0_i, static_cast<DT *>(d_out))
+    // terms from lanes up to n = 20, where few waves hide a scalar load's latency, by scalar loads beyond (us,
+    // lanes / scalar loads: n = 14 19 / 23, dense n = 18 27 / 35, n = 20 54 / 57; n = 21 99 / 94, n = 24 731 / 696,
+    // 3-regular n = 28 3030 / 2950)
+    const bool lanes = n <= 20;
+#define QQ_COST_DIAG(INT, DT)                                                                                      \
+    if (lanes)                                                                                                     \
+        hipLaunchKernelGGL((cost_diag_kernel<INT, true, DT>), grid, block, 0, s, n, dim, d_ell, d_ell_i, npairs,     \
+                           d_pair_ij, d_pair_b, d_pair_bi, c0, c0_i, static_cast<DT *>(d_out));                     \
+    else                                                                                                           \
+        hipLaunchKernelGGL((cost_diag_kernel<INT, false, DT>), grid, block, 0, s, n, dim, d_ell, d_ell_i, npairs,    \
+                           d_pair_ij, d_pair_b, d_pair_bi, c0, c0_i, static_cast<DT *>(d_out))
     switch (diag_type) {
     case DIAG_F64: QQ_COST_DIAG(false, double); break;
     case DIAG_I32: QQ_COST_DIAG(true, int32_t); break;
