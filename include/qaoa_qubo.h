@@ -116,6 +116,18 @@ qq_status qq_problem_create(int n, const double *H, const double *f, double c0, 
 
 qq_status qq_problem_destroy(qq_problem *prob);
 
+/*
+ * Device memory that the library keeps.  Calls on host buffers (and calls
+ * without a workspace) and handles take their device memory from blocks kept
+ * for reuse: up to 4 GiB per device while a problem lives on it, up to 256 MiB
+ * afterwards.  A library allocation that would fail frees them first; for
+ * another allocator in the process that runs out, qq_trim_memory frees every
+ * kept block of a device (those in use by live handles and running calls are
+ * not kept blocks).  bytes (may be NULL): how much that was.  Any thread, at
+ * any time.  Errors: QQ_E_INVALID (no such device), QQ_E_DEVICE.
+ */
+qq_status qq_trim_memory(int device, size_t *bytes);
+
 /* Summary of the problem (see qq_info).  Host call; no device work. */
 qq_status qq_problem_info(const qq_problem *prob, qq_info *out);
 

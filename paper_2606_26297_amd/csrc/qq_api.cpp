@@ -14,6 +14,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <initializer_list>
 #include <memory>
 #include <new>
 #include <string>
@@ -194,18 +195,34 @@ struct qq_problem {
     // the same tables of the QPU-local terms (linear ones and the constant among them) and of the cross-QPU
     // couplings (qq_set_allocation), read by the partitioned phases (complex128 both, complex64 the cross part's)
     std::vector<CostTab> ltabs, xtabs;
-    DevBuf ltab_buf, xtab_buf, xthr_buf;  // xthr_buf: both forms' per-thread constants
+    // an allocation's device memory: its small arrays with both forms' per-thread constants (one block), the
+    // local tables, the cross diagonal and the two forms' cost tables
+    DevBuf part_buf, local_buf, cross_buf, ltab_buf, xtab_buf;
 
+    // Gives the buffers back; evaluations on the caller's streams may still read them until the device is idle.
+    static void give_back(std::initializer_list<DevBuf *> bufs)
+    {
+        bool any = false;
+        for (DevBuf *b : bufs) any = any || b->p;
+        if (any && hipDeviceSynchronize() == hipSuccess)
+            for (DevBuf *b : bufs) b->done();
+        for (DevBuf *b : bufs) b->release();
+    }
+    void drop_allocation()
+    {
+        give_back({&part_buf, &local_buf, &cross_buf, &ltab_buf, &xtab_buf});
+        ltabs.clear();
+        xtabs.clear();
+        d_qpu = nullptr;
+        d_tables = d_cross = nullptr;
+        d_part = nullptr;
+        d_part_cq = nullptr;
+        num_qpus = 0;
+    }
     ~qq_problem()
     {
-        void *ptrs[] = {d_qpu, d_tables, d_cross, d_part, d_part_cq};
         if (dim) (void)hipSetDevice(device);
-        for (void *q : ptrs)
-            if (q) (void)hipFree(q);
-        // evaluations on the caller's streams may still read the handle's memory
-        if (diag_buf.p && hipDeviceSynchronize() == hipSuccess)
-            for (DevBuf *b : {&diag_buf, &coef_buf, &ctab_buf, &ltab_buf, &xtab_buf, &xthr_buf}) b->done();
-        for (DevBuf *b : {&diag_buf, &coef_buf, &ctab_buf, &ltab_buf, &xtab_buf, &xthr_buf}) b->release();
+        give_back({&diag_buf, &coef_buf, &ctab_buf, &part_buf, &local_buf, &cross_buf, &ltab_buf, &xtab_buf});
         if (counted) pool_problem_removed(device);
     }
 };
@@ -664,7 +681,7 @@ qq_status build_tables(int device, int n, const double *d_ell, const double *d_b
     QQ_HIP(launch_table_constants(n, runs, d_ell, d_b, d_thr, stream));
     const uint64_t T = tiles_per_state(n);
     const size_t per = (size_t)T * kCostRow, need = per * tabs.size() * sizeof(double);
-    if (buf.get(device, need) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) for the cost tables failed", need);
+    if (buf.get(device, need, true) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) for the cost tables failed", need);
     for (size_t k = 0; k < tabs.size(); ++k) {
         qq_problem::CostTab &tb = tabs[k];
         double *rows = static_cast<double *>(buf.p) + k * per;
@@ -674,6 +691,15 @@ qq_status build_tables(int device, int n, const double *d_ell, const double *d_b
         QQ_HIP(launch_cost_table(n, tb.high, tb.pos4, tb.pos8, lq, rq, T, d_ell, np, d_pij, d_pb, c0, rows, stream));
     }
     return QQ_OK;
+}
+
+// Appends an array to a host block (256-byte aligned); its offset.
+size_t pack(std::vector<char> &host, const void *src, size_t bytes)
+{
+    const size_t at = align_up(host.size());
+    host.resize(at + std::max<size_t>(bytes, 16));
+    if (bytes) std::memcpy(host.data() + at, src, bytes);
+    return at;
 }
 
 const qq_problem::CostTab *find_table(const std::vector<qq_problem::CostTab> &tabs, const SetDesc &sd, int lane_q)
@@ -1652,7 +1678,7 @@ qq_status qq_problem_create(int n, const double *H, const double *f, double c0, 
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     QQ_HIP(hipSetDevice(device));
     const int np = (int)pb->pair_b.size();
-    if (pb->diag_buf.get(device, dbytes) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) for the diagonal failed", dbytes);
+    if (pb->diag_buf.get(device, dbytes, true) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) for the diagonal failed", dbytes);
     pb->d_diag = pb->diag_buf.p;
     pb->counted = true;
     pool_problem_added(device);
@@ -1671,17 +1697,12 @@ qq_status qq_problem_create(int n, const double *H, const double *f, double c0, 
     for (int i = 0; i < n; ++i)
         for (int j = i + 1; j < n; ++j) bsym[(size_t)i * n + j] = bsym[(size_t)j * n + i] = pb->b[(size_t)i * n + j];
     std::vector<char> host;
-    auto put = [&](const void *src, size_t bytes) {
-        const size_t at = align_up(host.size());
-        host.resize(at + std::max<size_t>(bytes, 16));
-        if (bytes) std::memcpy(host.data() + at, src, bytes);
-        return at;
-    };
+    auto put = [&](const void *src, size_t bytes) { return pack(host, src, bytes); };
     const size_t o_ell = put(pb->ell.data(), sizeof(double) * n), o_elli = put(pb->ell_i.data(), sizeof(int32_t) * n),
                  o_pij = put(pb->pair_ij.data(), sizeof(int32_t) * 2 * np), o_pb = put(pb->pair_b.data(), sizeof(double) * np),
                  o_pbi = put(pb->pair_bi.data(), sizeof(int32_t) * np), o_regq = put(regq.data(), sizeof(double) * regq.size()),
                  o_b = put(bsym.data(), sizeof(double) * bsym.size()), o_thr = align_up(host.size());
-    QQ_HIP(pb->coef_buf.get(device, o_thr + 256 * 8 * sizeof(double) * pb->ctabs.size()));
+    QQ_HIP(pb->coef_buf.get(device, o_thr + 256 * 8 * sizeof(double) * pb->ctabs.size(), true));
     char *coef = static_cast<char *>(pb->coef_buf.p);
     QQ_HIP(hipMemcpyAsync(coef, host.data(), host.size(), hipMemcpyHostToDevice, stream));
     pb->d_ell = reinterpret_cast<double *>(coef + o_ell);
@@ -1728,6 +1749,21 @@ qq_status qq_problem_create(int n, const double *H, const double *f, double c0, 
     pb->cmax = mx;
     pb->argmin = mi;
     *out = guard.release();
+    return QQ_OK;
+}
+
+qq_status qq_trim_memory(int device, size_t *bytes)
+{
+    g_err.clear();
+    int count = 0;
+    if (hipGetDeviceCount(&count) != hipSuccess) {
+        (void)hipGetLastError();
+        count = 0;
+    }
+    if (device < 0 || device >= count) return fail(QQ_E_INVALID, "device %d outside [0, %d)", device, count);
+    QQ_HIP(hipSetDevice(device));
+    const size_t freed = pool_trim(device);
+    if (bytes) *bytes = freed;
     return QQ_OK;
 }
 
@@ -1858,101 +1894,74 @@ qq_status qq_set_allocation(qq_problem *pb, int M, const int32_t *qpu_of_var, co
         st != QQ_OK)
         return st;
     QQ_HIP(hipSetDevice(pb->device));
-    // release a previous allocation
-    void *olds[] = {pb->d_qpu, pb->d_tables, pb->d_cross, pb->d_part, pb->d_part_cq};
-    for (void *q : olds)
-        if (q) QQ_HIP(hipFree(q));
-    pb->ltab_buf.release();
-    pb->xtab_buf.release();
-    pb->xthr_buf.release();
-    pb->ltabs.clear();
-    pb->xtabs.clear();
-    pb->d_qpu = nullptr;
-    pb->d_tables = pb->d_cross = nullptr;
-    pb->d_part = nullptr;
-    pb->d_part_cq = nullptr;
-    pb->num_qpus = 0;
+    pb->drop_allocation();
     hipStream_t stream = nullptr;
-    QQ_HIP(hipMalloc((void **)&pb->d_qpu, sizeof(int32_t) * n));
-    QQ_HIP(hipMalloc(&pb->d_tables, total * es));
-    QQ_HIP(hipMalloc((void **)&pb->d_part, sizeof(PartDesc)));
-    {
-        // pair sums of every factor among each run of four consecutive qubits (see d_part_cq)
-        const int runs = std::max(1, n - 3);
-        std::vector<double> pcq((size_t)(M + 1) * runs * 16, 0.0);
-        for (int f = 0; f <= M; ++f)
-            for (int q = 0; q + 4 <= n; ++q)
-                for (int r = 1; r < 16; ++r) {
-                    const int j = __builtin_ctz(r), a = q + j;
-                    double sum = 0.0;
-                    for (int k = j + 1; k < 4; ++k) {
-                        if (!((r >> k) & 1)) continue;
-                        const int c = q + k;
-                        const bool local = qpu_of_var[a] == qpu_of_var[c];
-                        if ((f == M && !local) || (f < M && local && qpu_of_var[a] == f)) sum += pb->b[(size_t)a * n + c];
-                    }
-                    pcq[((size_t)f * runs + q) * 16 + r] = sum;
+    // pair sums of every factor among each run of four consecutive qubits (see d_part_cq)
+    const int runs = std::max(1, n - 3);
+    std::vector<double> pcq((size_t)(M + 1) * runs * 16, 0.0);
+    for (int f = 0; f <= M; ++f)
+        for (int q = 0; q + 4 <= n; ++q)
+            for (int r = 1; r < 16; ++r) {
+                const int j = __builtin_ctz(r), a = q + j;
+                double sum = 0.0;
+                for (int k = j + 1; k < 4; ++k) {
+                    if (!((r >> k) & 1)) continue;
+                    const int c = q + k;
+                    const bool local = qpu_of_var[a] == qpu_of_var[c];
+                    if ((f == M && !local) || (f < M && local && qpu_of_var[a] == f)) sum += pb->b[(size_t)a * n + c];
                 }
-        QQ_HIP(hipMalloc((void **)&pb->d_part_cq, sizeof(double) * pcq.size()));
-        QQ_HIP(hipMemcpy(pb->d_part_cq, pcq.data(), sizeof(double) * pcq.size(), hipMemcpyHostToDevice));
-    }
-    QQ_HIP(hipMemcpy(pb->d_qpu, qpu_of_var, sizeof(int32_t) * n, hipMemcpyHostToDevice));
-    QQ_HIP(hipMemcpy(pb->d_part, &pd, sizeof(PartDesc), hipMemcpyHostToDevice));
+                pcq[((size_t)f * runs + q) * 16 + r] = sum;
+            }
+    // the two forms' symmetric matrices
+    std::vector<double> bl((size_t)n * n, 0.0), bx((size_t)n * n, 0.0);
+    for (int i = 0; i < n; ++i)
+        for (int j = i + 1; j < n; ++j) {
+            auto &form = qpu_of_var[i] == qpu_of_var[j] ? bl : bx;
+            form[(size_t)i * n + j] = form[(size_t)j * n + i] = pb->b[(size_t)i * n + j];
+        }
+    const int nx = (int)xb.size(), nl = (int)lb.size();
+    const std::vector<double> zeros(n, 0.0);
+    pb->ltabs = pb->xtabs = cost_table_list(n);
+    const size_t nthr = 256 * 8 * pb->ltabs.size();
+    std::vector<char> host;
+    auto put = [&](const void *src, size_t bytes) { return pack(host, src, bytes); };
+    const size_t o_qpu = put(qpu_of_var, sizeof(int32_t) * n), o_pd = put(&pd, sizeof pd),
+                 o_pcq = put(pcq.data(), sizeof(double) * pcq.size()), o_zero = put(zeros.data(), sizeof(double) * n),
+                 o_xij = put(xij.data(), sizeof(int32_t) * 2 * nx), o_xb = put(xb.data(), sizeof(double) * nx),
+                 o_xbi = put(xbi.data(), sizeof(int32_t) * nx), o_lij = put(lij.data(), sizeof(int32_t) * 2 * nl),
+                 o_lb = put(lb.data(), sizeof(double) * nl), o_bl = put(bl.data(), sizeof(double) * bl.size()),
+                 o_bx = put(bx.data(), sizeof(double) * bx.size()), o_thr = align_up(host.size());
+    if (pb->part_buf.get(pb->device, o_thr + 2 * nthr * sizeof(double), true) != hipSuccess ||
+        pb->local_buf.get(pb->device, total * es, true) != hipSuccess)
+        return fail(QQ_E_NOMEM, "hipMalloc(%zu) for the local tables failed", (size_t)total * es);
+    if (need_cross && pb->cross_buf.get(pb->device, (size_t)pb->dim * es, true) != hipSuccess)
+        return fail(QQ_E_NOMEM, "hipMalloc(%zu) for the cross diagonal failed", (size_t)pb->dim * es);
+    char *mem = static_cast<char *>(pb->part_buf.p);
+    auto f64 = [&](size_t at) { return reinterpret_cast<double *>(mem + at); };
+    auto i32 = [&](size_t at) { return reinterpret_cast<int32_t *>(mem + at); };
+    pb->d_qpu = i32(o_qpu);
+    pb->d_part = reinterpret_cast<PartDesc *>(mem + o_pd);
+    pb->d_part_cq = f64(o_pcq);
+    pb->d_tables = pb->local_buf.p;
+    pb->d_cross = pb->cross_buf.p;
+    QQ_HIP(hipMemcpyAsync(mem, host.data(), host.size(), hipMemcpyHostToDevice, stream));
     QQ_HIP(launch_local_tables(n, pb->diag_type, pb->d_part, pb->d_ell, pb->d_ell_i, (int)pb->pair_b.size(),
                                pb->d_pair_ij, pb->d_pair_b, pb->d_pair_bi, pb->d_qpu, pb->c0, pb->c0_i, pb->d_tables,
                                total, stream));
-    {
-        const int nx = (int)xb.size(), nl = (int)lb.size();
-        const std::vector<double> zeros(n, 0.0);
-        DevBuf zero_ell, zero_elli, dij, db, dbi, dlij, dlb;
-        auto put = [&](DevBuf &buf, const void *src, size_t bytes) -> hipError_t {
-            if (hipError_t e = buf.get(pb->device, std::max<size_t>(bytes, 16)); e != hipSuccess) return e;
-            return bytes ? hipMemcpy(buf.p, src, bytes, hipMemcpyHostToDevice) : hipSuccess;
-        };
-        QQ_HIP(put(zero_ell, zeros.data(), sizeof(double) * n));
-        QQ_HIP(put(zero_elli, zeros.data(), sizeof(int32_t) * n));
-        QQ_HIP(put(dij, xij.data(), sizeof(int32_t) * 2 * nx));
-        QQ_HIP(put(db, xb.data(), sizeof(double) * nx));
-        QQ_HIP(put(dbi, xbi.data(), sizeof(int32_t) * nx));
-        QQ_HIP(put(dlij, lij.data(), sizeof(int32_t) * 2 * nl));
-        QQ_HIP(put(dlb, lb.data(), sizeof(double) * nl));
-        // cross diagonal: the cost diagonal of the cross couplings alone (no linear terms, no constant)
-        if (need_cross) {
-            if (hipMalloc(&pb->d_cross, (size_t)pb->dim * es) != hipSuccess)
-                return fail(QQ_E_NOMEM, "hipMalloc for the cross diagonal failed");
-            QQ_HIP(launch_cost_diag(n, pb->diag_type, static_cast<double *>(zero_ell.p),
-                                    static_cast<int32_t *>(zero_elli.p), nx, static_cast<int32_t *>(dij.p),
-                                    static_cast<double *>(db.p), static_cast<int32_t *>(dbi.p), 0.0, 0, pb->d_cross,
-                                    pb->dim, stream));
-        }
-        // the tables of the two parts (the partitioned phases of n > 12)
-        auto B = [&](int i, int j) {
-            return i < j ? pb->b[(size_t)i * n + j] : pb->b[(size_t)j * n + i];
-        };
-        pb->ltabs = pb->xtabs = cost_table_list(n);
-        std::vector<double> bl((size_t)n * n, 0.0), bx((size_t)n * n, 0.0);
-        for (int i = 0; i < n; ++i)
-            for (int j = 0; j < n; ++j)
-                if (i != j) (qpu_of_var[i] == qpu_of_var[j] ? bl : bx)[(size_t)i * n + j] = B(i, j);
-        DevBuf dbl, dbx;
-        QQ_HIP(put(dbl, bl.data(), sizeof(double) * bl.size()));
-        QQ_HIP(put(dbx, bx.data(), sizeof(double) * bx.size()));
-        const size_t nthr = 256 * 8 * pb->ltabs.size();
-        QQ_HIP(pb->xthr_buf.get(pb->device, std::max<size_t>(16, 2 * nthr * sizeof(double))));
-        double *d_thr = static_cast<double *>(pb->xthr_buf.p);
-        if (qq_status st = build_tables(pb->device, n, pb->d_ell, static_cast<double *>(dbl.p), nl,
-                                        static_cast<int32_t *>(dlij.p), static_cast<double *>(dlb.p), pb->c0, pb->ltabs,
-                                        pb->ltab_buf, d_thr, stream);
-            st != QQ_OK)
-            return st;
-        if (qq_status st = build_tables(pb->device, n, static_cast<double *>(zero_ell.p), static_cast<double *>(dbx.p),
-                                        nx, static_cast<int32_t *>(dij.p), static_cast<double *>(db.p), 0.0, pb->xtabs,
-                                        pb->xtab_buf, d_thr + nthr, stream);
-            st != QQ_OK)
-            return st;
-        QQ_HIP(hipDeviceSynchronize());
-        for (DevBuf *q : {&zero_ell, &zero_elli, &dij, &db, &dbi, &dlij, &dlb, &dbl, &dbx}) q->done();
-    }
+    // cross diagonal: the cost diagonal of the cross couplings alone (no linear terms, no constant)
+    if (need_cross)
+        QQ_HIP(launch_cost_diag(n, pb->diag_type, f64(o_zero), i32(o_zero), nx, i32(o_xij), f64(o_xb), i32(o_xbi), 0.0, 0,
+                                pb->d_cross, pb->dim, stream));
+    // the tables of the two parts (the partitioned phases of n > 12)
+    if (qq_status st = build_tables(pb->device, n, pb->d_ell, f64(o_bl), nl, i32(o_lij), f64(o_lb), pb->c0, pb->ltabs,
+                                    pb->ltab_buf, f64(o_thr), stream);
+        st != QQ_OK)
+        return st;
+    if (qq_status st = build_tables(pb->device, n, f64(o_zero), f64(o_bx), nx, i32(o_xij), f64(o_xb), 0.0, pb->xtabs,
+                                    pb->xtab_buf, f64(o_thr) + nthr, stream);
+        st != QQ_OK)
+        return st;
+    QQ_HIP(hipDeviceSynchronize());
     pb->num_qpus = M;
     pb->qpu.assign(qpu_of_var, qpu_of_var + n);
     pb->cross_terms = cross;
@@ -2709,7 +2718,7 @@ qq_status qq_graph_create(qq_problem *pb, int p, int batch, int flags, const dou
                  o_s = o_h + align_up((size_t)std::max(1, history) * batch * 8), total = o_s + 256;
     QQ_HIP(hipSetDevice(g->device));
     if (qq_status st = check_device_fits(g->device, total, "the optimiser workspace"); st != QQ_OK) return st;
-    if (g->mem.get(g->device, total) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) failed", total);
+    if (g->mem.get(g->device, total, true) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) failed", total);
     char *base = static_cast<char *>(g->mem.p);
     g->ws = base;
     g->m = reinterpret_cast<double *>(base + o_m);

@@ -53,7 +53,20 @@ void free_all(const std::vector<Block> &v)
 
 }  // namespace
 
-hipError_t DevBuf::get(int dev, size_t n)
+size_t pool_trim(int device)
+{
+    std::vector<Block> all;
+    {
+        std::lock_guard<std::mutex> lock(mutex());
+        all = evict(pool(device), 0);
+    }
+    size_t bytes = 0;
+    for (const Block &b : all) bytes += b.bytes;
+    free_all(all);
+    return bytes;
+}
+
+hipError_t DevBuf::get(int dev, size_t n, bool lasting)
 {
     release();
     device = dev;
@@ -62,11 +75,12 @@ hipError_t DevBuf::get(int dev, size_t n)
     {
         std::lock_guard<std::mutex> lock(mutex());
         Pool &q = pool(dev);
-        // the smallest block that fits and is at most twice the request (or 1 MiB)
+        // the smallest block that fits and is not too large
+        const size_t most = lasting ? want + want / 8 : want > (512u << 10) ? 2 * want : (size_t)(1u << 20);
         size_t best = q.free.size();
         for (size_t i = 0; i < q.free.size(); ++i) {
             const size_t b = q.free[i].bytes;
-            if (b < want || b > (want > (512u << 10) ? 2 * want : (size_t)(1u << 20))) continue;
+            if (b < want || b > most) continue;
             if (best == q.free.size() || b < q.free[best].bytes) best = i;
         }
         if (best != q.free.size()) {
@@ -79,16 +93,11 @@ hipError_t DevBuf::get(int dev, size_t n)
     }
     hipError_t e = hipMalloc(&p, want);
     if (e != hipSuccess) {
+        (void)hipGetLastError();  // not for the next launch's check to find
         // the kept blocks may be what is missing
-        std::vector<Block> all;
-        {
-            std::lock_guard<std::mutex> lock(mutex());
-            all = evict(pool(dev), 0);
-        }
-        if (!all.empty()) {
-            free_all(all);
-            (void)hipGetLastError();
+        if (pool_trim(dev) > 0) {
             e = hipMalloc(&p, want);
+            if (e != hipSuccess) (void)hipGetLastError();
         }
     }
     if (e != hipSuccess) {
@@ -101,10 +110,12 @@ hipError_t DevBuf::get(int dev, size_t n)
 
 void DevBuf::release()
 {
+    const bool was_idle = idle;
+    idle = false;
     if (!p) return;
     std::vector<Block> out;
     bool kept = false;
-    if (idle && bytes <= kPoolKeep) {
+    if (was_idle && bytes <= kPoolKeep) {
         std::lock_guard<std::mutex> lock(mutex());
         Pool &q = pool(device);
         if (bytes <= bound(q)) {
@@ -118,7 +129,6 @@ void DevBuf::release()
     if (!kept) (void)hipFree(p);
     p = nullptr;
     bytes = 0;
-    idle = false;
 }
 
 void pool_problem_added(int device)

@@ -10,6 +10,11 @@
 // A block enters the pool only idle: its owner has synchronised the stream (or the device) that used it,
 // so any thread may take it for any stream.  A block of unknown state is freed with hipFree, which waits
 // for the device.  Its contents are whatever the last owner left.
+//
+// A request for a call takes a kept block of up to twice its size (1 MiB for the small ones); one for a handle,
+// which may live as long as the program, of at most an eighth more, so that a handle does not sit on memory
+// that it has no use for.  pool_trim gives every kept block back to the device, as a failing allocation of the
+// library's own does before it is tried again.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -32,12 +37,15 @@ struct DevBuf {
     DevBuf(const DevBuf &) = delete;
     DevBuf &operator=(const DevBuf &) = delete;
     ~DevBuf() { release(); }
-    // At least n bytes on `device` (made current by the caller).
-    hipError_t get(int dev, size_t n);
+    // At least n bytes on `device` (made current by the caller); lasting: for a handle.
+    hipError_t get(int dev, size_t n, bool lasting = false);
     // Nothing on the device uses the block any more.
     void done() { idle = true; }
     void release();
 };
+
+// Frees every kept block of the (current) device; their bytes.
+size_t pool_trim(int device);
 
 // Problems alive on a device, for the pool's bound.
 void pool_problem_added(int device);

@@ -111,6 +111,7 @@ SIGNATURES = {
     "qq_device_count": ([ctypes.POINTER(_int)], _int),
     "qq_problem_create": ([_int, _dp, _dp, ctypes.c_double, _int, _vp, ctypes.POINTER(_vp)], _int),
     "qq_problem_destroy": ([_vp], _int),
+    "qq_trim_memory": ([_int, _szp], _int),
     "qq_problem_info": ([_vp, ctypes.POINTER(QQInfo)], _int),
     "qq_coefficients": ([_vp, _dp, _dp, _dp, _dp, _dp], _int),
     "qq_cost_diagonal": ([_vp, _vp, _int, _vp], _int),
@@ -313,6 +314,13 @@ def qq_problem_create(n, H, f=None, c0=0.0, device=0, stream=None):
 
 def qq_problem_destroy(handle):
     _check(lib().qq_problem_destroy(handle))
+
+
+def qq_trim_memory(device=0) -> int:
+    """Frees the device memory kept for reuse on a device; the bytes freed."""
+    freed = ctypes.c_size_t(0)
+    _check(lib().qq_trim_memory(int(device), ctypes.byref(freed)))
+    return freed.value
 
 
 def qq_problem_info(handle) -> QQInfo:
