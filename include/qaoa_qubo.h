@@ -237,8 +237,8 @@ qq_status qq_topk(qq_problem *prob, int p, const double *params, int flags, int 
  * QQ_E_NOMEM, QQ_E_DEVICE.
  */
 typedef struct {
-    int tiles_per_chunk;   /* tiles (4096 amplitudes) per work item of a multi-pass problem; 0: chosen from the
-                              batch, with the same results whatever the choice */
+    int tiles_per_chunk;   /* most tiles (4096 amplitudes) per work item of a multi-pass problem; the launch takes
+                              fewer where its batch is small (with the same results); 0: no limit but that */
     int max_workgroups;    /* cap on the persistent grid; 0: every workgroup that fits on the device at once */
     double wait_limit_ms;  /* bound on one dependency wait; 0: 2000 ms */
 } qq_many_options;
@@ -333,7 +333,7 @@ qq_status qq_evaluate_many_guarded(int count, qq_problem *const *problems, const
  * A schedule fixes, for one (p, batch, flags) of a problem:
  *   workgroups_per_state  G: workgroups that share one state in every pass
  *                         (power of two, 1 <= G <= 2^(n-12)); default
- *                         min(2^(n-12), 4096 / batch) rounded down to a power of two
+ *                         min(2^(n-12), 16384 / batch) rounded down to a power of two
  *   set_pairing           which 4-qubit runs above qubit 11 share a high pass when
  *                         n - 12 is a multiple of 8 with at least four runs
  *                         (0: run i with run m-1-i, 1: adjacent runs, 2: run i with
@@ -358,9 +358,12 @@ qq_status qq_evaluate_many_guarded(int count, qq_problem *const *problems, const
  * double it; then the other set order, where one applies, at the best of those.  It pins the
  * fastest and, if cache_path is not
  * NULL, appends it to that JSON-lines file; an entry already there for the same
- * device, n, p, batch, planning flags and diagonal width is used without timing.
+ * device, n, p, batch, planning flags and diagonal width, measured on the same
+ * revision of the kernels, is used without timing.
  * qq_autotune_many does the same for qq_evaluate_many over tiles_per_chunk in
- * {4, 8, 16, 24, 32, 48, 64} and max_workgroups in {0, 2 x compute units}, keyed by a
+ * {4, 8, 16, 24, 32, 48, 64} (the limits that differ for the batch; one that its
+ * items stay below leaves them to the launch) and max_workgroups in {0, 2 x compute
+ * units}, keyed by a
  * hash of every problem's (n, p, batch, diagonal width); it returns the options
  * (to pass to qq_evaluate_many) and the measured time in ms_out (may be NULL).
  * Both allocate their own device memory and synchronise `stream`.

@@ -1066,12 +1066,27 @@ bool cache_lookup(const char *path, const std::string &key, std::string &line_ou
     return found;
 }
 
-qq_status cache_append(const char *path, const std::string &line)
+// An entry's key, and the form that entries took before they carried a revision.  The revision stands for the
+// kernels that the choice was measured on: an entry of another one is tuned again.
+constexpr int kTuneRevision = 2;
+struct TuneKey {
+    std::string now, before;
+    explicit TuneKey(const char *fields) : now(fields), before(fields)
+    {
+        char rev[32];
+        std::snprintf(rev, sizeof rev, "\"rev\":%d,", kTuneRevision);
+        now += rev;
+    }
+};
+
+qq_status cache_append(const char *path, const TuneKey &key, const char *tail)
 {
     if (!path) return QQ_OK;
     FILE *f = std::fopen(path, "a");
+    std::string line;
+    if (!f && cache_lookup(path, key.before, line)) return QQ_OK;  // a read-only file with an entry of its own stays usable
     if (!f) return fail(QQ_E_INVALID, "cannot open the tuning cache %s for appending", path);
-    std::fputs(line.c_str(), f);
+    std::fputs((key.now + tail).c_str(), f);
     std::fputc('\n', f);
     std::fclose(f);
     return QQ_OK;
@@ -1137,7 +1152,7 @@ uint64_t fnv1a(uint64_t h, int64_t v)
     return h;
 }
 
-// Tiles per item when the caller leaves them open, for one launch (one diagonal type).  An item costs the launch a
+// Tiles per item unless the caller sets a lower limit, for one launch (one diagonal type).  An item costs the launch a
 // share of one ticket, one wait, one set of coefficients and one completion (o = 0.0145 us of the whole chip in
 // complex64, 0.046 in complex128: one-tile items against the best, 512 and 128 problems), so `items` one-tile items
 // cost items * o / c at c tiles each; the longest chain of dependent passes runs its tiles one after the other in
@@ -1153,8 +1168,8 @@ int many_tiles_per_chunk(double items, int longest, bool c128)
     return (int)std::min(64.0, std::max(1.0, std::nearbyint(std::sqrt(items * o / (std::max(1, longest) * u)))));
 }
 
-// Tiles per partial sum (log2) when the caller leaves the item size open: the problem's own, whatever the batch, so
-// that its results do not depend on the batch.  At most 256 sums per pass up to n = 24, so that items as small as
+// Tiles per partial sum (log2; fewer where a caller's limit is no multiple): the problem's own, whatever the batch,
+// so that its results do not depend on the batch.  At most 256 sums per pass up to n = 24, so that items as small as
 // a batch can want (one tile up to n = 20, four at n = 22) remain possible; a sum per tile costs an item about 3% of
 // its time.
 int many_unit_log2(uint64_t tiles)
@@ -1249,14 +1264,12 @@ qq_status plan_many(int count, qq_problem *const *pbs, const int *p, const int *
                 G.bytes += (double)pb->dim * diag_bytes_of(pb->diag_type);
             } else {
                 I.shift = c128 ? 0.0 : pb->alpha;  // the complex64 pass bodies accumulate with C - alpha
-                if (opt && opt->tiles_per_chunk > 0) {
-                    I.tpc = (int)std::min<uint64_t>((uint64_t)opt->tiles_per_chunk, I.tiles);
-                    I.unit_log2 = __builtin_ctz((unsigned)I.tpc);
-                } else {  // the multiple of the unit next to the launch's choice
-                    I.unit_log2 = many_unit_log2(I.tiles);
-                    const int unit = 1 << I.unit_log2;
-                    I.tpc = (int)std::min<uint64_t>((uint64_t)std::max(1, (open_tpc + unit / 2) / unit) * unit, I.tiles);
-                }
+                // the multiple of the unit next to the launch's choice, which the caller may limit
+                const int limit = opt ? opt->tiles_per_chunk : 0;
+                I.unit_log2 = many_unit_log2(I.tiles);
+                if (limit > 0) I.unit_log2 = std::min(I.unit_log2, __builtin_ctz((unsigned)limit));
+                const int unit = 1 << I.unit_log2, want = limit > 0 ? std::min(limit, open_tpc) : open_tpc;
+                I.tpc = (int)std::min<uint64_t>((uint64_t)std::max(1, (want + unit / 2) / unit) * unit, I.tiles);
                 I.nunits = (int)(I.tiles >> I.unit_log2);
                 I.nchunks = (int)((I.tiles + (uint64_t)I.tpc - 1) / (uint64_t)I.tpc);
                 I.npasses = (int)plan.passes.size();
@@ -2867,9 +2880,9 @@ qq_status qq_autotune(qq_problem *pb, int p, int batch, int flags, const char *c
                   "{\"kind\":\"evaluate\",\"device\":\"%s\",\"n\":%d,\"p\":%d,\"batch\":%d,\"flags\":%d,"
                   "\"diag_bytes\":%d,",
                   device_tag(pb->device).c_str(), pb->n, p, batch, sched_flags(flags), diag_bytes_of(pb->diag_type));
-    const std::string key(keybuf);
+    const TuneKey key(keybuf);
     std::string line;
-    if (cache_lookup(cache_path, key, line)) {
+    if (cache_lookup(cache_path, key.now, line)) {
         double G = 0, pr = 0, ms = 0, order = 0, so = 0;
         if (json_num(line, "G", G) && json_num(line, "pairing", pr) && json_num(line, "ms", ms) &&
             json_num(line, "tile_order", order) && json_num(line, "set_order", so)) {
@@ -2944,7 +2957,7 @@ qq_status qq_autotune(qq_problem *pb, int p, int batch, int flags, const char *c
     char tail[200];
     std::snprintf(tail, sizeof tail, "\"G\":%d,\"pairing\":%d,\"tile_order\":%d,\"set_order\":%d,\"ms\":%.4f}",
                   bestG, bestP, bestO, bestS, best);
-    if (qq_status st = cache_append(cache_path, key + tail); st != QQ_OK) return st;
+    if (qq_status st = cache_append(cache_path, key, tail); st != QQ_OK) return st;
     *out = qq_schedule{bestG, bestP, best, 1, 0, tried, bestO, bestS};
     return QQ_OK;
 }
@@ -2967,9 +2980,9 @@ qq_status qq_autotune_many(int count, qq_problem *const *problems, const int *p,
     char keybuf[512];
     std::snprintf(keybuf, sizeof keybuf, "{\"kind\":\"many\",\"device\":\"%s\",\"count\":%d,\"flags\":%d,\"shape\":\"%016llx\",",
                   device_tag(device).c_str(), count, sched_flags(flags), (unsigned long long)h);
-    const std::string key(keybuf);
+    const TuneKey key(keybuf);
     std::string line;
-    if (cache_lookup(cache_path, key, line)) {
+    if (cache_lookup(cache_path, key.now, line)) {
         double tpc = 0, mw = 0, ms = 0;
         if (json_num(line, "tiles_per_chunk", tpc) && json_num(line, "max_workgroups", mw) && json_num(line, "ms", ms) &&
             tpc >= 1 && mw >= 0) {
@@ -3010,20 +3023,30 @@ qq_status qq_autotune_many(int count, qq_problem *const *problems, const int *p,
         }
     }
     const int eflags = flags | QQ_ENERGY | QQ_PARAMS_ON_DEVICE | QQ_OUT_ON_DEVICE;
+    // limits that leave every item as an earlier one does are not timed again
     std::vector<qq_many_options> cands;
-    for (int tpc : {4, 8, 16, 24, 32, 48, 64})
-        for (int mw : {0, 2 * cus}) cands.push_back({tpc, mw, 0.0});
+    std::vector<std::vector<int>> seen;
     size_t need = 0;
-    for (const auto &c : cands) {
+    for (int tpc : {4, 8, 16, 24, 32, 48, 64}) {
+        const qq_many_options c{tpc, 0, 0.0};
         ManyLayout M;
         if (qq_status st = plan_many(count, problems, p, batch, eflags, &c, M); st != QQ_OK) return st;
         need = std::max(need, M.total);
+        std::vector<int> split;
+        for (const ManyGroup &G : M.groups)
+            for (const ManyInst &I : G.inst) {
+                split.push_back(I.tpc);
+                split.push_back(I.unit_log2);
+            }
+        if (std::find(seen.begin(), seen.end(), split) != seen.end()) continue;
+        seen.push_back(split);
+        for (int mw : {0, 2 * cus}) cands.push_back({tpc, mw, 0.0});
     }
     if (qq_status st = check_device_fits(device, need, "the tuning workspace"); st != QQ_OK) return st;
     DevBuf ws;
     if (ws.get(device, need) != hipSuccess) return fail(QQ_E_NOMEM, "hipMalloc(%zu) for tuning failed", need);
     double best = INFINITY;
-    qq_many_options bopt{16, 0, 0.0};
+    qq_many_options bopt = cands[0];
     for (const auto &c : cands) {
         double ms = 0;
         auto run = [&]() {
@@ -3039,7 +3062,7 @@ qq_status qq_autotune_many(int count, qq_problem *const *problems, const int *p,
     char tail[160];
     std::snprintf(tail, sizeof tail, "\"tiles_per_chunk\":%d,\"max_workgroups\":%d,\"ms\":%.4f}", bopt.tiles_per_chunk,
                   bopt.max_workgroups, best);
-    if (qq_status st = cache_append(cache_path, key + tail); st != QQ_OK) return st;
+    if (qq_status st = cache_append(cache_path, key, tail); st != QQ_OK) return st;
     *out = bopt;
     if (ms_out) *ms_out = best;
     return QQ_OK;
