@@ -716,58 +716,22 @@ qq_status run_plan(qq_problem *pb, const Plan &plan, const Layout &L, int p, int
     const bool prof = g_prof && !capturing;  // no event records inside a captured graph
     const bool c128 = flags & QQ_C128;
     const uint64_t T = tiles_per_state(pb->n);
-    const size_t es = c128 ? 16 : 8;
-    (void)es;
     if (plan.nslots > kMaxSlots) return fail(QQ_E_UNSUPPORTED, "plan needs %d accumulator slots (max %d)", plan.nslots, kMaxSlots);
-    const bool use_fast = fast_plan(pb, plan);
-    // a single pass (n <= 12, one workgroup per set) writes the results itself
-    const bool single = plan.sets.size() == 1;
+    // a plan's only pass (n <= 12, one workgroup per set) writes the results itself
+    const bool use_fast = fast_plan(pb, plan), single = !use_fast;
     const double escale = pb->n < kTileBits ? std::ldexp(1.0, pb->n - kTileBits) : 1.0;
+    const double amp0 = 1.0 / std::sqrt((double)pb->dim);
     int slot_base = 0;
     for (const auto &pp : plan.passes) {
         if ((int)pp.ops.size() > kMaxOps) return fail(QQ_E_UNSUPPORTED, "pass has %zu ops (max %d)", pp.ops.size(), kMaxOps);
         const SetDesc &sd = plan.sets[pp.set];
-        PassArgs a;
-        std::memset(&a, 0, sizeof a);
-        a.n = pb->n;
-        a.p = p;
-        a.B = B;
-        a.G = L.G;
-        a.tiles = T;
-        a.dim_mask = pb->dim - 1;
-        a.pos4 = sd.pos4;
-        a.pos8 = sd.pos8;
-        a.high = sd.high;
-        a.w1 = sd.pos4 - 4;
-        a.w2 = sd.pos8 - sd.pos4 - 4;
-        a.flags = pp.flags;
-        a.nops = (int)pp.ops.size();
-        a.nslots = (int)pp.slot_out.size();
-        a.slot_base = slot_base;
-        a.slot_stride = B * L.G;
-        a.amp0 = 1.0 / std::sqrt((double)pb->dim);
-        a.params = d_params;
-        a.diag = pb->d_diag;
-        a.psi = ws + L.psi;
-        a.lam = ws + L.lam;
-        a.state_stride = L.stride;
-        a.partial = reinterpret_cast<double *>(ws + L.partial);
-        a.part_tables = pb->d_tables;
-        a.cross_diag = pb->d_cross;
-        a.part = pb->d_part;
-        for (size_t i = 0; i < pp.ops.size(); ++i) a.ops[i] = pp.ops[i];
-        if (single) {
-            a.out = out;
-            a.escale = escale;
-            for (size_t i = 0; i < pp.slot_out.size(); ++i) a.slot_out[i] = (uint8_t)pp.slot_out[i];
-        }
         ProfRec rec{};
         if (prof) {
             QQ_HIP(hipEventCreate(&rec.start));
             QQ_HIP(hipEventCreate(&rec.stop));
             QQ_HIP(hipEventRecord(rec.start, stream));
         }
-        if (use_fast && pp.fkind >= 0) {
+        if (use_fast) {
             FastPassParams fp;
             fp.blocked = L.blocked;
             fp.part = (flags & QQ_PARTITIONED) &&
@@ -788,15 +752,15 @@ qq_status run_plan(qq_problem *pb, const Plan &plan, const Layout &L, int p, int
             fp.store_psi = (pp.flags & PF_STORE_PSI) ? 1 : 0;
             fp.slot_base = slot_base;
             fp.slot_stride = B * L.G;
-            fp.amp0 = a.amp0;
+            fp.amp0 = amp0;
             fp.params = d_params;
             fp.diag = pb->d_diag;
-            fp.psi = a.psi;
-            fp.lam = a.lam;
+            fp.psi = ws + L.psi;
+            fp.lam = ws + L.lam;
             fp.state_stride = L.stride;
             fp.pre = ws + L.pre;
             fp.ilv = L.ilv;
-            fp.partial = a.partial;
+            fp.partial = reinterpret_cast<double *>(ws + L.partial);
             fp.cq = pb->d_regq + 16 * (pp.fkind == FK_FIRST ? sd.pos8 : sd.pos4);
             fp.part_cq = pb->d_part_cq;
             fp.part_cq_runs = std::max(1, pb->n - 3);
@@ -818,24 +782,41 @@ qq_status run_plan(qq_problem *pb, const Plan &plan, const Layout &L, int p, int
             }
             if (c128) QQ_HIP(launch_fast_pass128(pp.fkind, sd.high != 0, fp, stream));
             else QQ_HIP(launch_fast_pass(pp.fkind, sd.high != 0, pb->diag_type, fp, stream));
-        } else if (single && c128 && !(flags & QQ_PARTITIONED)) {
+        } else if (c128 && !(flags & QQ_PARTITIONED)) {
             SingleArgs sa;
             sa.n = pb->n;
             sa.p = p;
-            sa.amp0 = a.amp0;
+            sa.amp0 = amp0;
             sa.escale = escale;
             sa.params = d_params;
             sa.diag = pb->d_diag;
-            sa.psi = (pp.flags & PF_STORE_PSI) ? a.psi : nullptr;
+            sa.psi = (pp.flags & PF_STORE_PSI) ? ws + L.psi : nullptr;
             sa.out = out;
             QQ_HIP(launch_single128(sa, B, pp.nstates > 1, pb->diag_type, stream));
         } else {
-            QQ_HIP(launch_pass(a, c128, pp.nstates, pb->diag_type, stream));
+            OneTileArgs a;
+            std::memset(&a, 0, sizeof a);
+            a.p = p;
+            a.nops = (int)pp.ops.size();
+            a.nslots = (int)pp.slot_out.size();
+            a.mask = (uint32_t)(pb->dim - 1);
+            a.amp0 = amp0;
+            a.escale = escale;
+            a.params = d_params;
+            a.diag = pb->d_diag;
+            a.psi = (pp.flags & PF_STORE_PSI) ? ws + L.psi : nullptr;
+            a.part_tables = pb->d_tables;
+            a.cross_diag = pb->d_cross;
+            a.part = pb->d_part;
+            a.out = out;
+            for (size_t i = 0; i < pp.slot_out.size(); ++i) a.slot_out[i] = (uint8_t)pp.slot_out[i];
+            for (size_t i = 0; i < pp.ops.size(); ++i) a.ops[i] = pp.ops[i];
+            QQ_HIP(launch_pass(a, B, c128, pp.nstates, pb->diag_type, stream));
         }
         if (prof) {
             QQ_HIP(hipEventRecord(rec.stop, stream));
             rec.meta.kind = pp.nstates > 1 ? 2 : 1;
-            rec.meta.pass_kind = (use_fast && pp.fkind >= 0) ? pp.fkind : -1;
+            rec.meta.pass_kind = use_fast ? pp.fkind : -1;
             rec.meta.part = (flags & QQ_PARTITIONED) && (pp.fkind == FK_FIRST || pp.fkind == FK_TURN ||
                                                           pp.fkind == FK_BTURN || !use_fast) ? 1 : 0;
             rec.meta.high = sd.high;
@@ -844,10 +825,10 @@ qq_status run_plan(qq_problem *pb, const Plan &plan, const Layout &L, int p, int
             rec.meta.c128 = c128;
             rec.meta.n = pb->n;
             rec.meta.batch = B;
-            rec.meta.bytes = pass_bytes(pb, pp, B, c128, use_fast && pp.fkind >= 0);
+            rec.meta.bytes = pass_bytes(pb, pp, B, c128, use_fast);
             g_prof_log.push_back(rec);
         }
-        slot_base += a.nslots;
+        slot_base += (int)pp.slot_out.size();
     }
     if (single) return QQ_OK;
     FinalizeArgs fa;
@@ -858,7 +839,7 @@ qq_status run_plan(qq_problem *pb, const Plan &plan, const Layout &L, int p, int
     fa.nslots = plan.nslots;
     fa.escale = escale;
     // the complex64 specialised kernels accumulate with C - alpha (every pass of a multi-pass plan)
-    fa.shift = (use_fast && !c128 && !plan.passes.empty() && plan.passes[0].fkind >= 0) ? pb->alpha : 0.0;
+    fa.shift = c128 ? 0.0 : pb->alpha;
     fa.partial = reinterpret_cast<const double *>(ws + L.partial);
     fa.out = out;
     int s = 0;

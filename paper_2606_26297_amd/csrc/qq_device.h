@@ -69,17 +69,6 @@ __device__ __forceinline__ uint64_t uni64(uint64_t x)
     return ((uint64_t)hi << 32) | lo;
 }
 
-template <typename T>
-__device__ __forceinline__ T ld_at(uint64_t ubase, uint64_t voff)
-{
-    return *reinterpret_cast<const T *>(ubase + voff);
-}
-template <typename T>
-__device__ __forceinline__ void st_at(uint64_t ubase, uint64_t voff, T v)
-{
-    *reinterpret_cast<T *>(ubase + voff) = v;
-}
-
 // Tile-local index held by thread t in register r under layout L:
 //   L = 2: register bits are tile bits 8..11, thread bits are tile bits 0..7
 //   L = 1: register bits are tile bits 4..7,  thread bits are tile bits 0..3, 8..11

@@ -82,35 +82,20 @@ struct EvalOut {
     int estride, gstride;
 };
 
-struct PassArgs {
-    int n;
+// One-tile evaluations (n <= 12) as operations, one workgroup per parameter set, results written by the kernel.
+struct OneTileArgs {
     int p;
-    int B;            // states in this launch
-    int G;            // workgroups per state
-    uint64_t tiles;   // tiles per state
-    uint64_t dim_mask;
-    int pos4, pos8;   // qubits of tile bits 4..7 (pos4..pos4+3) and 8..11 (pos8..pos8+3), pos4 + 4 <= pos8
-    int high;         // 0: tile bits are qubits 0..11 (pos4 = 4, pos8 = 8)
-    int w1, w2;       // tile-index bits below pos4 (above qubit 3) and between the runs
-    uint32_t flags;
-    int nops;
-    int nslots;
-    int slot_base;
-    int slot_stride;  // B * G
-    double amp0;
+    int nops, nslots;
+    uint32_t mask;  // 2^n - 1
+    double amp0, escale;  // escale: 2^(n-12) (replicated tile)
     const double *params;  // device [B][2p]
     const void *diag;
-    void *psi;
-    void *lam;
-    uint64_t state_stride;
-    double *partial;
+    void *psi;  // [B][2^n] final states, or NULL
     const void *part_tables;  // packed local tables (diag element type)
     const void *cross_diag;   // 2^n cross diagonal (diag element type)
     const PartDesc *part;     // device
-    // a plan's only pass writes the results itself: slot s is output slot_out[s]
     EvalOut out;
-    double escale;
-    uint8_t slot_out[kMaxImmSlots];
+    uint8_t slot_out[kMaxImmSlots];  // output of each slot
     Op ops[kMaxOps];
 };
 
@@ -127,7 +112,7 @@ struct FinalizeArgs {
 };
 
 // Kernel launchers (qq_kernels.hip).
-hipError_t launch_pass(const PassArgs &a, bool c128, int nstates, int diag_type, hipStream_t s);
+hipError_t launch_pass(const OneTileArgs &a, int B, bool c128, int nstates, int diag_type, hipStream_t s);
 hipError_t launch_finalize(const FinalizeArgs &a, hipStream_t s);
 hipError_t launch_cost_diag(int n, int diag_type, const double *d_ell, const int32_t *d_ell_i, int npairs,
                             const int32_t *d_pair_ij, const double *d_pair_b, const int32_t *d_pair_bi, double c0,

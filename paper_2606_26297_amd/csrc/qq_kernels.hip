@@ -27,24 +27,18 @@ namespace {
 using namespace dev;
 
 template <typename R, int NS, typename DT>
-__global__ void __launch_bounds__(kThreads) pass_kernel(const PassArgs a)
+__global__ void __launch_bounds__(kThreads) pass_kernel(const OneTileArgs a)
 {
     __shared__ gen::GenShared<R> sh;
-    const int t = threadIdx.x;
-    int b, g;
-    block_coords(a.B, a.G, b, g);
+    const int t = threadIdx.x, b = blockIdx.x;
     gen::gen_setup<R>(sh, a.params + (size_t)b * 2 * a.p, a.p, t);
     double acc[kMaxLocalSlots] = {0.0, 0.0, 0.0, 0.0};
-    gen::gen_tiles<R, NS, DT>(a, sh, t, b, (uint64_t)g, a.tiles, (uint64_t)a.G, acc);
+    gen::gen_tile<R, NS, DT>(a, sh, t, b, acc);
     // fixed-order workgroup reduction of the FP64 accumulators
     gen::gen_slot_totals<R>(a.nslots, acc, sh, t, [&](int s, double sum) __attribute__((always_inline)) {
-        if (a.out.energy) {  // the plan's only pass, one workgroup per set
-            const int o = a.slot_out[s];
-            if (o == 0) a.out.energy[(size_t)b * a.out.estride] = sum * a.escale;
-            else a.out.grad[(size_t)b * a.out.gstride + (o - 1)] = sum * (2.0 * a.escale);
-            return;
-        }
-        a.partial[(size_t)(a.slot_base + s) * a.slot_stride + (size_t)b * a.G + g] = sum;
+        const int o = a.slot_out[s];
+        if (o == 0) a.out.energy[(size_t)b * a.out.estride] = sum * a.escale;
+        else a.out.grad[(size_t)b * a.out.gstride + (o - 1)] = sum * (2.0 * a.escale);
     });
 }
 
@@ -465,9 +459,9 @@ __global__ void __launch_bounds__(256) topk_stage2(const double *cp, const uint6
 }
 
 template <typename R, int NS>
-hipError_t launch_pass_t(const PassArgs &a, int diag_type, hipStream_t s)
+hipError_t launch_pass_t(const OneTileArgs &a, int B, int diag_type, hipStream_t s)
 {
-    const dim3 grid((unsigned)(a.B * a.G)), block(kThreads);
+    const dim3 grid((unsigned)B), block(kThreads);
     switch (diag_type) {
     case DIAG_F64: hipLaunchKernelGGL((pass_kernel<R, NS, double>), grid, block, 0, s, a); break;
     case DIAG_I32: hipLaunchKernelGGL((pass_kernel<R, NS, int32_t>), grid, block, 0, s, a); break;
@@ -486,10 +480,10 @@ unsigned grid_for(uint64_t work, unsigned cap = 8192)
 
 }  // namespace
 
-hipError_t launch_pass(const PassArgs &a, bool c128, int nstates, int diag_type, hipStream_t s)
+hipError_t launch_pass(const OneTileArgs &a, int B, bool c128, int nstates, int diag_type, hipStream_t s)
 {
-    if (c128) return nstates > 1 ? launch_pass_t<double, 2>(a, diag_type, s) : launch_pass_t<double, 1>(a, diag_type, s);
-    return nstates > 1 ? launch_pass_t<float, 2>(a, diag_type, s) : launch_pass_t<float, 1>(a, diag_type, s);
+    if (c128) return nstates > 1 ? launch_pass_t<double, 2>(a, B, diag_type, s) : launch_pass_t<double, 1>(a, B, diag_type, s);
+    return nstates > 1 ? launch_pass_t<float, 2>(a, B, diag_type, s) : launch_pass_t<float, 1>(a, B, diag_type, s);
 }
 
 hipError_t launch_finalize(const FinalizeArgs &a, hipStream_t s)
