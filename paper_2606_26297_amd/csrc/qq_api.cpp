@@ -480,13 +480,21 @@ Plan make_plan(int n, int p, int mode, int pairing = 0, int set_order = 0)
 
 uint64_t tiles_per_state(int n) { return n <= kTileBits ? 1ull : (1ull << (n - kTileBits)); }
 
-// Workgroups per state: 16384 over the batch, which leaves a few tiles to each at the largest sizes and one
-// at the small ones.  Against 4096: n = 28, eight states, gradient 329 -> 322 ms; n = 20, 256 states, energies
-// 3.52 -> 3.39 ms; n = 27, two states, partitioned 12.42 -> 12.33; below 4096 tiles in all the same.
-int choose_G(int n, int B)
+// Workgroups per state: 16384 over the batch, or one per tile where the batch has fewer tiles (32 tiles to each at
+// n = 28 with eight states, 256 with 64).  Against 4096: n = 28, eight states, gradient 329 -> 322 ms; n = 20, 256
+// states, energies 3.52 -> 3.39 ms; n = 27, two states, partitioned 12.4 either way; the same workgroups up to
+// 4096 tiles in all.
+// Complex64 batches of 16 and more at n = 20 to 22 take 128 at most: a state's tiles in one to four workgroup waves,
+// and that few per state, lose 5 to 20% there, whatever the depth (energies at 128 / 256 / 512 / 1024, us:
+// n = 20, 32 states 427 / 491, 64 states 855 / 1014; n = 21, 32 states 1658 / 2007 / 1829; n = 22, 16 states
+// 1676 / 1989 / 1785 / 1816; gradients n = 20, 32 states 1292 / 1482; n = 21, 16 states 2447 / 2785 / 2640).  Elsewhere
+// that limit loses: n = 23, 16 states, gradient 9.67 -> 10.07 ms; n = 21, ten states, energies 491 -> 524 us;
+// complex128, n = 20, 48 states, gradient 4.91 -> 5.19.
+int choose_G(int n, int B, bool c128)
 {
     const uint64_t T = tiles_per_state(n);
     uint64_t target = std::max<uint64_t>(1, 16384 / (uint64_t)B);
+    if (!c128 && B >= 16 && T >= 256 && T <= 1024) target = std::min<uint64_t>(target, 128);
     uint64_t G = 1;
     while (G * 2 <= target && G * 2 <= T) G *= 2;
     return (int)G;
@@ -532,7 +540,7 @@ Layout make_layout(const qq_problem *pb, int p, int B, int flags, const Plan &pl
     }
     L.stride = L.ilv ? 2 * (size_t)pb->dim : (size_t)pb->dim;
     const size_t state = L.stride * es * (size_t)B;
-    L.G = G > 0 ? G : choose_G(pb->n, B);
+    L.G = G > 0 ? G : choose_G(pb->n, B, flags & QQ_C128);
     L.nslots = plan.nslots;
     size_t off = 0;
     L.psi = off;
@@ -2841,7 +2849,7 @@ qq_status qq_get_schedule(const qq_problem *pb, int p, int batch, int flags, qq_
         out->ms = e->ms;
         out->pinned = 1;
     } else {
-        out->workgroups_per_state = choose_G(pb->n, batch);
+        out->workgroups_per_state = choose_G(pb->n, batch, flags & QQ_C128);
         out->set_pairing = 0;
         out->set_order = default_set_order(pb->n);
     }
@@ -2879,7 +2887,7 @@ qq_status qq_autotune(qq_problem *pb, int p, int batch, int flags, const char *c
     // tile order, default set order); stage 2: the blocked tile order at the best pairing, for the
     // best G, half and double; stage 3: the other set order at the best of those
     const uint64_t T = tiles_per_state(pb->n);
-    const int G0 = choose_G(pb->n, batch);
+    const int G0 = choose_G(pb->n, batch, flags & QQ_C128);
     auto g_candidates = [&](int Gc) {
         std::vector<int> v;
         for (int G : {Gc / 2, Gc, Gc * 2})
