@@ -1158,14 +1158,16 @@ int many_tiles_per_chunk(double items, int longest, bool c128)
 }
 
 // Tiles per partial sum (log2; fewer where a caller's limit is no multiple): the problem's own, whatever the batch,
-// so that its results do not depend on the batch.  At most 256 sums per pass up to n = 24, so that items as small as
-// a batch can want (one tile up to n = 20, four at n = 22) remain possible; a sum per tile costs an item about 3% of
-// its time.
+// so that its results do not depend on the batch.  At most 256 sums per pass up to n = 23 and 1024 at n = 24 and 25, so
+// that items as small as a batch can want (one tile up to n = 20, four at n = 22, eight at n = 24) remain possible; a
+// sum per tile costs an item about 3% of its time.  Units of 8 / 16 tiles, gradients, ms: n = 24, one problem
+// 1.23 / 1.24, complex128 1.91 / 2.90; two problems 2.12 / 2.53 and 4.37 / 4.95; n = 25, one problem 1.91 / 2.02 and
+// 3.74 / 3.83; n = 26 3.52 / 3.37 and 7.17 / 7.84.
 int many_unit_log2(uint64_t tiles)
 {
     int k = 0;
-    while (k < 4 && (tiles >> (k + 9))) ++k;
-    return k;
+    while (k < 3 && (tiles >> (k + 9))) ++k;
+    return tiles >> 14 ? 4 : k;
 }
 
 qq_status plan_many(int count, qq_problem *const *pbs, const int *p, const int *batch, int flags,
