@@ -26,6 +26,14 @@
 // no cache write-back, and a waiting workgroup no invalidate.  Measured against a
 // release and an acquire per item (XCD-wide cache operations): 512 problems 18.9
 // against 20.5 ms, 128 problems 4.75 against 6.0, 96 problems 1.45 against 1.75.
+// The language's memory model gives relaxed operations no order across addresses; what orders them here is
+// the hardware and the compiled code.  A wave's agent-scope stores and loads are performed at the memory
+// side of the L2s (write-through stores, loads that bypass the caches above), s_waitcnt(0) returns only once
+// the wave's stores are acknowledged there, and the workgroup barriers, which the compiler moves no memory
+// access across, keep thread 0's increment behind every wave's wait and every wave's loads behind thread
+// 0's poll.  A compiler or target that kept any of these accesses in a cache of the XCD, moved one across
+// a barrier or the wait, or let the wait end before the acknowledgement would need the release and
+// acquire that FENCED adds (drain_queue).  The bitwise tests over grids and batches would show it.
 // The complex128 launch keeps ordinary 16-byte accesses with a release and an
 // acquire per item (its amplitudes as two 8-byte atomics: 12.6 against 10.4 ms).
 //

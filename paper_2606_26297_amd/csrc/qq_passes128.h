@@ -96,7 +96,8 @@ __device__ __forceinline__ void gst(uint64_t sbase, O voff, double2 x)
 
 // Transpose between two layouts.  Two-state kinds: one round of 16-byte words through 69.6 KB of LDS
 // (two workgroups per compute unit, which their registers allow).  One-state kinds: the real parts,
-// then the imaginary parts, through 34.8 KB (four workgroups per compute unit).
+// then the imaginary parts, through 34.8 KB (room for the three workgroups per compute unit that the registers
+// of the kinds with a phase or an energy allow, and the four of the middle pass).
 template <int FROM, int TO>
 __device__ __forceinline__ void xpose(double2 *lds, double2 (&v)[kRegs], int t)
 {

@@ -5,10 +5,10 @@
 // A shot with uniform u in [0, 1) takes the first basis index z whose cumulative probability
 // sum_{y <= z} P(y) exceeds u * sum_y P(y) (inverse transform in basis order).  The search is
 // hierarchical: blocks of 4096 consecutive indices, each summed row by row (64 consecutive entries
-// per row, one per lane), and a prefix over the block sums (formed on the host in index order);
-// a shot finds its block by binary search over that prefix, then scans the block's rows with the
-// same row sums, so a block's scan ends exactly at the sum the prefix used.  All sums are FP64 in
-// a fixed order; results are reproducible.
+// per row, one per lane) with every row's running sum kept, and a prefix over the block sums (formed on
+// the host in index order); a shot finds its block by probes of 64 prefix sums, its row by one read of the
+// block's row sums and its entry by that row's scan, which forms the same sums again, so a block's search
+// ends exactly at the sum the prefix used.  All sums are FP64 in a fixed order; results are reproducible.
 #include "qq_device.h"
 
 namespace qq {
